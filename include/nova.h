@@ -223,7 +223,7 @@ int nova_llm_decode_noalloc(const nova_llm* llm, const int32_t* ids, const int32
  * linear co-run table, and Sec. 3.2.3): one linear layer out[M, N] += x[M, K] w[N, K]^T
  * (x, w device bf16 row-major, out device fp32, all 256-byte aligned), enqueued on `stream`,
  * with one of the kernels the stage calls use or the low-footprint pair of the intra-CU variant:
- *  NOVA_LINEAR_TILED       the encode / prefill GEMM (256x256 or 128x128 tiles as for the stages;
+ *  NOVA_LINEAR_TILED       the encode / prefill GEMM (tiles chosen by size as for the stages;
  *                          K % 64 == 0, N % 128 == 0)
  *  NOVA_LINEAR_TILED_SMALL the same GEMM held to 128x128 tiles of 4 waves (64 KB of LDS), so a
  *                          CU keeps room for another kernel's workgroups

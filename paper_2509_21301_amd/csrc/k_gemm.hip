@@ -4,8 +4,10 @@
 // and prefill time (the paper's Table 3 and Sec. 3.2.1).  Design for gfx950:
 //  * bf16 MFMA 16x16x32 (fp32 accumulate); 4 or 8 waves per workgroup, each owning a WM x WN tile;
 //  * bf16 activations: A and W tiles go global -> LDS by 16-byte LDS-DMA loads in an XOR-swizzled
-//    layout (conflict-free fragment reads), two stages, the DMA of step k+1 in flight during the
-//    MFMAs of step k;
+//    layout (conflict-free fragment reads).  Problems that fill the GPU run 256x256 tiles over two
+//    stages, the DMA of step k+1 in flight during the MFMAs of step k; smaller ones run 32x64 to
+//    128x256 tiles through a ring of 3 to 6 stages, K cut into slices while CUs are left idle
+//    (plan_gemm picks tile and slices by estimated time);
 //  * fp32 activations (tiny-stack exact mode): tiles staged through registers (split into bf16
 //    hi + lo parts, two MFMAs each, since weights are exactly bf16) into a padded LDS layout;
 //  * tile order remapped so that each XCD (which owns one L2) works on a contiguous block of
@@ -13,6 +15,9 @@
 //  * the epilogue (bias, GELU, SwiGLU, residual or position add) runs through LDS so that every
 //    global access covers whole cache lines.
 // Requirements (checked by the host): N % 128 == 0, K % 64 == 0, 16-byte aligned rows, ldo % 4 == 0.
+#include <algorithm>
+#include <cmath>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -539,19 +544,161 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_dma_kernel(Ge
   gemm_epilogue<OT, EPI, WM, WN>(p, acc, reinterpret_cast<float*>(smem), wave, lane, m0 + wm * WM, n0 + wn * WN);
 }
 
-// Sum of the K-slice partials in slice order, then the epilogue: STORE out = OT(sum + bias),
-// RESID out += sum + bias (fp32).  One thread per 4 consecutive outputs.
+// BM x BN tiles through a ring of NST LDS stages of 64 along K, for problems that leave the GPU partly
+// idle: there the two-stage kernel above is bound by latency (about 1 us per K step of a 128x128 tile,
+// of which its MFMAs are 0.26 us: every step waits for the DMA issued one step earlier).  Here the DMA
+// of step kt + NST - 1 is issued while step kt is multiplied, a wave waits only for the oldest stage
+// (counted by vmcnt, so the DMA is the untracked form), and one barrier per step both publishes that
+// stage and frees the one read before it.  0.52 us per step of a 128x128 tile on 8 waves (64x32 each: a
+// third faster than 4 waves of 64x64 when one workgroup has the CU to itself), 0.2 us for 32x64.
+// Weights from HBM, M x N x K: 16 x 3584 x 18944 78 -> 28 us, 64 x 3840 x 1280 24 -> 6.6 us, 203 x
+// 4608 x 3584 37 -> 20 us, 2304 x 1280 x 1280 22 -> 14 us.
+template <typename OT, int EPI, int BM, int BN, int WM, int WN, int NST>
+__global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_ring_kernel(GemmArgs p) {
+  constexpr int TM = WM / 16, TN = WN / 16;
+  constexpr int WAVES_N = BN / WN;
+  constexpr int NW = (BM / WM) * (BN / WN);
+  constexpr int STAGE = (BM + BN) * BK;              // bf16 per stage
+  constexpr int IT = (BM + BN) / 8 / NW;             // DMA instructions per wave per stage
+  static_assert(IT * NW * 8 == BM + BN, "tile rows must split into 8-row DMA groups");
+  static_assert((NST - 2) * IT < 64, "vmcnt range");
+  extern __shared__ __align__(16) unsigned char smem[];
+  bf16_t* lds = reinterpret_cast<bf16_t*>(smem);
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+
+  const int nm = (p.M + BM - 1) / BM, nn = p.N / BN;
+  const int total = nm * nn;
+  const int idg = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int ks = p.kslice ? idg / total : 0;
+  const int id = idg - ks * total;
+  constexpr int G = 8;
+  const int group = id / (G * nn);
+  const int first_m = group * G;
+  const int gsize = min(nm - first_m, G);
+  const int within = id % (G * nn);
+  const int m0 = (first_m + within % gsize) * BM, n0 = (within / gsize) * BN;
+
+  const size_t k_off = (size_t)ks * p.kslice;
+  const bf16_t* A = reinterpret_cast<const bf16_t*>(p.A) + k_off;
+  const bf16_t* W = p.W + k_off;
+  const int lrow = lane >> 3, lslot = lane & 7;
+  const bf16_t* src[IT];
+#pragma unroll
+  for (int t = 0; t < IT; ++t) {
+    const int r = (wave * IT + t) * 8 + lrow;        // row of the stage: A rows, then W rows
+    const int c = 8 * (lslot ^ ((r >> 1) & 7));
+    src[t] = r < BM ? A + (size_t)min(m0 + r, p.M - 1) * p.lda + c : W + (size_t)(n0 + r - BM) * p.ldw + c;
+  }
+  const uint32_t lbase = lds_addr_of(lds) + (uint32_t)(wave * IT * 8 * BK) * 2u;
+  auto dma = [&](int kt, int stage) {
+#pragma unroll
+    for (int t = 0; t < IT; ++t)
+      lds_dma16_untracked(src[t] + kt * BK, lbase + (uint32_t)(stage * STAGE + t * 8 * BK) * 2u);
+  };
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int fr = lane & 15, fk = lane >> 4;
+  const int sw = (fr >> 1) & 7;
+  const int off0 = fr * BK + 8 * (fk ^ sw), off1 = fr * BK + 8 * ((fk + 4) ^ sw);
+  const int nk = (p.kslice ? min(p.kslice, p.K - (int)k_off) : p.K) / BK;
+
+#pragma unroll
+  for (int st = 0; st < NST - 1; ++st)
+    if (st < nk) dma(st, st);
+  int rs = 0, ws = NST - 1;                          // stage read, stage refilled
+  auto step = [&](int refill) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (refill >= 0) dma(refill, ws);
+    const bf16_t* a = lds + rs * STAGE + wm * WM * BK;
+    const bf16_t* b = lds + rs * STAGE + (BM + wn * WN) * BK;
+    Frag8 fa[2][TM], fb[2][TN];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[s][i] = *reinterpret_cast<const Frag8*>(a + i * 16 * BK + (s ? off1 : off0));
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[s][j] = *reinterpret_cast<const Frag8*>(b + j * 16 * BK + (s ? off1 : off0));
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma16(fa[s][i], fb[s][j], acc[i][j]);
+    __builtin_amdgcn_sched_barrier(0);               // the MFMAs stay above the next step's wait
+    rs = rs + 1 == NST ? 0 : rs + 1;
+    ws = ws + 1 == NST ? 0 : ws + 1;
+  };
+  // s_waitcnt operand: at most n DMA instructions outstanding, and every fragment read returned
+  constexpr auto vm = [](int n) constexpr { return 0x0070 | (n & 15) | ((n >> 4) << 14); };
+  int kt = 0;
+  for (; kt + NST - 2 < nk; ++kt) {
+    __builtin_amdgcn_s_waitcnt(vm((NST - 2) * IT));
+    step(kt + NST - 1 < nk ? kt + NST - 1 : -1);
+  }
+  auto last = [&](auto younger) {                    // one of the last steps, `younger` stages behind it
+    constexpr int J = decltype(younger)::value;
+    if constexpr (J <= NST - 3) {
+      if (nk > J) {
+        __builtin_amdgcn_s_waitcnt(vm(J * IT));
+        step(-1);
+      }
+    }
+  };
+  static_assert(NST >= 2 && NST <= 6, "ring depth");
+  last(std::integral_constant<int, 3>{});
+  last(std::integral_constant<int, 2>{});
+  last(std::integral_constant<int, 1>{});
+  last(std::integral_constant<int, 0>{});
+  __syncthreads();                                   // the epilogue reuses the stages
+  if constexpr (EPI == EPI_STORE && sizeof(OT) == 4) {
+    if (p.kslice) {
+      GemmArgs q = p;
+      q.out = reinterpret_cast<float*>(p.out) + (size_t)ks * p.split_stride;
+      q.bias = nullptr;
+      gemm_epilogue<OT, EPI, WM, WN>(q, acc, reinterpret_cast<float*>(smem), wave, lane, m0 + wm * WM, n0 + wn * WN);
+      return;
+    }
+  }
+  gemm_epilogue<OT, EPI, WM, WN>(p, acc, reinterpret_cast<float*>(smem), wave, lane, m0 + wm * WM, n0 + wn * WN);
+}
+
+// Sum of the K-slice partials in slice order, then the epilogue: STORE out = OT(sum + bias), GELU
+// out = OT(gelu(sum + bias)), RESID out += sum + bias (fp32), SWIGLU out = OT(silu(gate) * up) with
+// gate and up columns interleaved in blocks of 8.  One thread per 4 consecutive outputs.
 template <typename OT, int EPI>
 __global__ void __launch_bounds__(256) split_reduce_kernel(GemmArgs p, const float* __restrict__ part, int slices) {
   const long i4 = (long)blockIdx.x * 256 + threadIdx.x;
-  const int n4 = p.N / 4;
+  constexpr bool SW = EPI == EPI_SWIGLU;
+  const int n4 = p.N / (SW ? 8 : 4);
   if (i4 >= (long)p.M * n4) return;
-  const int m = (int)(i4 / n4), n = (int)(i4 % n4) * 4;
+  const int m = (int)(i4 / n4), q = (int)(i4 % n4);
+  const int n = SW ? (q >> 1) * 16 + (q & 1) * 4 : q * 4;
   const size_t stride = (size_t)p.M * p.N;
-  float4 v = *reinterpret_cast<const float4*>(part + (size_t)m * p.N + n);
-  for (int s = 1; s < slices; ++s) {
-    const float4 w = *reinterpret_cast<const float4*>(part + s * stride + (size_t)m * p.N + n);
-    v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+  auto sum = [&](int col) {
+    const float* src = part + (size_t)m * p.N + col;
+    float4 v = *reinterpret_cast<const float4*>(src);
+    for (int s = 1; s < slices; ++s) {
+      const float4 w = *reinterpret_cast<const float4*>(src + s * stride);
+      v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+    }
+    return v;
+  };
+  float4 v = sum(n);
+  if constexpr (SW) {
+    const float4 u = sum(n + 8);
+    const float o4[4] = {silu(v.x) * u.x, silu(v.y) * u.y, silu(v.z) * u.z, silu(v.w) * u.w};
+    store4<OT>(reinterpret_cast<OT*>(p.out) + (size_t)m * p.ldo + q * 4, o4);
+    return;
   }
   if (p.bias) {
     const uint2 bb = *reinterpret_cast<const uint2*>(p.bias + n);
@@ -563,7 +710,11 @@ __global__ void __launch_bounds__(256) split_reduce_kernel(GemmArgs p, const flo
     const float4 x = *o;
     *o = float4{x.x + v.x, x.y + v.y, x.z + v.z, x.w + v.w};
   } else {
-    const float o4[4] = {v.x, v.y, v.z, v.w};
+    float o4[4] = {v.x, v.y, v.z, v.w};
+    if constexpr (EPI == EPI_GELU) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o4[e] = gelu_erf(o4[e]);
+    }
     store4<OT>(reinterpret_cast<OT*>(p.out) + (size_t)m * p.ldo + n, o4);
   }
 }
@@ -604,25 +755,6 @@ static hipError_t launch_dma(const GemmArgs& p, hipStream_t s, int kslices = 1) 
   return hipGetLastError();
 }
 
-// K slices for a problem whose 128x128 tiles leave most of a last round idle: slices of at least
-// 1024 along K, a multiple of 64, chosen to fill whole rounds of 2 workgroups per CU best.
-static int split_slices(const GemmArgs& p) {
-  if (!p.split_ws) return 1;
-  const long tiles = (long)((p.M + 127) / 128) * (p.N / 128);
-  const long slots = 512;                         // 256 CUs, 2 workgroups each
-  if (tiles >= 2 * slots) return 1;
-  int best = 1;
-  double best_eff = (double)tiles / (double)(((tiles + slots - 1) / slots) * slots);
-  for (int sl = 2; sl <= 4; ++sl) {
-    if (p.K % (64 * sl) || p.K / sl < 1024) continue;
-    if ((size_t)sl * p.M * p.N > p.split_ws_floats) continue;
-    const long u = tiles * sl;
-    const double eff = (double)u / (double)(((u + slots - 1) / slots) * slots);
-    if (eff > best_eff + 0.05) { best = sl; best_eff = eff; }
-  }
-  return best;
-}
-
 // The output pointer moved by (rows, cols) elements: the residual and position epilogues write
 // fp32 whatever OT is.
 template <typename OT, int EPI>
@@ -633,62 +765,181 @@ static void* out_at(const GemmArgs& p, size_t rows, size_t cols) {
     return reinterpret_cast<OT*>(p.out) + rows * p.ldo + cols;
 }
 
-// Rows to run as 256x256 tiles ahead of the rest, which then run as 128x128 tiles (0: no split).
-// With many row tiles and a last round of 256x256 tiles (one workgroup per CU) that leaves much of
-// the GPU idle, the rows of whole rounds go first and the leftover rows second.  Cost in rounds of
-// 256x256 tiles: leftover 128x128 tiles that fit one workgroup per CU take about half a round,
-// each round of two per CU about 0.7; the split must save 0.3 of a round (the second launch's
-// ramp).  The screenshot encode (53 row tiles): QKV 4 -> 3.5 rounds, MLP up 5 -> 4.5, O and down
-// 2 -> 1.5; one 1008x1008 image's QKV (21 x 15 tiles): 2 -> 1.5; the 8-image MLP down (162 x 5):
-// 4 -> 3.5.
-static int row_split_rows(const GemmArgs& p) {
+// The K slices left in p.split_ws summed into the output by split_reduce_kernel, or left for the
+// caller to fold (p.slices_out).
+template <typename OT, int EPI>
+static hipError_t finish_slices(const GemmArgs& p, hipStream_t s, int slices) {
+  if (EPI == EPI_RESID && p.slices_out != nullptr && p.bias == nullptr) {
+    *p.slices_out = slices;
+    return hipSuccess;
+  }
+  const long n4 = (long)p.M * (p.N / (EPI == EPI_SWIGLU ? 8 : 4));
+  hipLaunchKernelGGL((split_reduce_kernel<OT, EPI>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, p,
+                     (const float*)p.split_ws, slices);
+  return hipGetLastError();
+}
+
+
+template <typename OT, int EPI, int BM, int BN, int WM, int WN, int NST>
+static hipError_t launch_ring(const GemmArgs& p, hipStream_t s, int kslices) {
+  constexpr size_t lds = (size_t)NST * (BM + BN) * BK * sizeof(bf16_t);
+  static_assert(lds <= 160 * 1024, "LDS");
+  static_assert((size_t)(BM / WM) * (BN / WN) * 16 * (WN + 4) * 4 <= lds, "epilogue scratch exceeds the stages");
+  auto kern = gemm_ring_kernel<OT, EPI, BM, BN, WM, WN, NST>;
+  static bool attr_set = false;   // benign race: idempotent attribute
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  const int nm = (p.M + BM - 1) / BM, nn = p.N / BN;
+  hipLaunchKernelGGL(kern, dim3(nm * nn * kslices), dim3((BM / WM) * (BN / WN) * 64), lds, s, p);
+  return hipGetLastError();
+}
+
+// The tiles a problem may run as, and the coefficients of a launch's estimated time in us, fitted to
+// 2900 timings (bf16 normal data, weights from HBM; M 16..5184 on the encoder's and decoder's nine
+// projection shapes, 1..12 K slices; 80% of the timings lie within 12% of the fit): with at most one
+// workgroup per CU, step1 per 64-wide K step + fixed1; with more, step2 per K step + round2 per round
+// of workgroup slots, + fixed2.
+struct Tile {
+  int bm, bn, per_cu;       // workgroups per CU
+  float step1, fixed1, step2, round2, fixed2;
+};
+static constexpr Tile kTiles[] = {
+    {32, 64, 2, 0.205f, 2.4f, 0.292f, 0.0f, 4.5f},    {64, 64, 2, 0.264f, 2.8f, 0.388f, 0.1f, 4.6f},
+    {64, 128, 1, 0.408f, 3.6f, 0.390f, 2.0f, 3.0f},   {128, 128, 1, 0.520f, 4.6f, 0.523f, 3.4f, 1.9f},
+    {256, 128, 1, 0.810f, 6.0f, 0.854f, 6.3f, -1.2f}, {128, 256, 1, 0.840f, 6.0f, 0.855f, 6.5f, -0.3f},
+    {128, 128, 2, 0.860f, 4.4f, 0.937f, 3.2f, 4.0f},  {256, 256, 1, 1.280f, 9.5f, 1.344f, 12.2f, -2.4f}};
+constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
+
+template <typename OT, int EPI>
+static hipError_t launch_plan_tile(const GemmArgs& p, int tile, hipStream_t s, int kslices) {
+  switch (tile) {
+    case 0: return launch_ring<OT, EPI, 32, 64, 16, 32, 6>(p, s, kslices);
+    case 1: return launch_ring<OT, EPI, 64, 64, 32, 32, 4>(p, s, kslices);
+    case 2: return launch_ring<OT, EPI, 64, 128, 64, 32, 4>(p, s, kslices);
+    case 3: return launch_ring<OT, EPI, 128, 128, 64, 32, 4>(p, s, kslices);
+    case 4: return launch_ring<OT, EPI, 256, 128, 64, 64, 3>(p, s, kslices);
+    case 5: return launch_ring<OT, EPI, 128, 256, 64, 64, 3>(p, s, kslices);
+    case 6: return launch_dma<OT, EPI, 128, 128, 64, 64>(p, s, kslices);
+    default: return launch_dma<OT, EPI, 256, 256, 64, 128>(p, s, kslices);
+  }
+}
+
+struct Plan {
+  int tile = -1, slices = 1;
+  int n1 = 0;               // columns of whole rounds that run first (0: one launch), the rest planned anew
+  double us = 1e30;
+};
+
+// Estimated time of `wgs` workgroups of tile t with `steps` K steps each, over weights of `bytes` (read
+// from HBM at 5 TB/s; the two bounds add as squares, which the timings near both fit best).
+static double tile_us(const Tile& t, long wgs, int steps, double bytes) {
+  const long slots = 256L * t.per_cu;
+  // a last round that is partly empty costs a whole one after a single round, and only its share
+  // after eight, when the workgroups have drifted apart (the 8-image QKV's 9.5 rounds take 9.5)
+  const double part = (double)wgs / (double)slots, whole = std::ceil(part);
+  const double rounds = whole - (whole - part) * std::min(1.0, (whole - 1.0) / 8.0);
+  const double us = wgs <= 256 ? steps * t.step1 + t.fixed1 : rounds * (steps * t.step2 + t.round2) + t.fixed2;
+  const double hbm = bytes / 5.0e6 + 2.0;
+  return std::sqrt(us * us + hbm * hbm);
+}
+
+// The plan of an M x N x K problem with the least estimated time: a tile, K slices (up to
+// max_slices, partials within ws_floats), and with `split_cols` the columns of whole rounds of one
+// tile first and the leftover columns, which would leave most of a last round idle, with another.
+static Plan plan_gemm(int M, int N, int K, int max_slices, size_t ws_floats, bool split_cols) {
+  Plan best;
+  for (int i = 0; i < kNumTiles; ++i) {
+    const Tile& t = kTiles[i];
+    if (N % t.bn) continue;
+    const int nm = (M + t.bm - 1) / t.bm;
+    const long tiles = (long)nm * (N / t.bn), slots = 256L * t.per_cu;
+    for (int sl = 1; sl <= max_slices; ++sl) {
+      const int steps = (K / BK + sl - 1) / sl;
+      if (sl > 1 && (K / BK - (sl - 1) * steps < 2 || (size_t)sl * M * N > ws_floats)) continue;
+      double us = tile_us(t, tiles * sl, steps, (double)N * K * 2);
+      if (sl > 1) {        // one more launch; the partials written and read, from the caches while they are few
+        const double bytes = (double)sl * M * N * 8;
+        us += 3.5 + bytes / (bytes < 64e6 ? 10.0e6 : 5.0e6);
+      }
+      if (us < best.us) best = {i, sl, 0, us};
+    }
+    if (split_cols && tiles > slots && tiles % slots) {
+      const int n1 = (int)(tiles / slots * slots / nm) * t.bn;
+      if (n1 <= 0 || n1 >= N) continue;
+      const double us = tile_us(t, (long)nm * (n1 / t.bn), K / BK, (double)n1 * K * 2) + 2.0 +
+                        plan_gemm(M, N - n1, K, max_slices, ws_floats, false).us;
+      if (us < best.us) best = {i, 1, n1, us};
+    }
+  }
+  return best;
+}
+
+template <typename OT, int EPI>
+static hipError_t launch_plan(const GemmArgs& p, hipStream_t s, bool split_cols) {
+  const int max_slices = EPI != EPI_POS && p.split_ws != nullptr && p.vt == nullptr ? 16 : 1;
+  // the position epilogue writes fp32 and reads the table: over many rows 256-wide tiles pay (41,472
+  // patches: 110 us against 122 us with 128x128 tiles)
+  if (EPI == EPI_POS && p.M > 4096 && p.N % 256 == 0) return launch_plan_tile<OT, EPI>(p, kNumTiles - 1, s, 1);
+  // one launch over all columns where the epilogue addresses more than the output by column (V^T, the
+  // position table) or the caller folds the slices
+  split_cols = split_cols && EPI != EPI_POS && p.vt == nullptr && p.slices_out == nullptr;
+  const Plan r = plan_gemm(p.M, p.N, p.K, max_slices, p.split_ws_floats, split_cols);
+  if (r.tile < 0) return hipErrorInvalidValue;
+  if (r.n1 > 0) {
+    GemmArgs a = p;
+    a.N = r.n1;
+    const hipError_t e = launch_plan_tile<OT, EPI>(a, r.tile, s, 1);
+    if (e != hipSuccess) return e;
+    GemmArgs b = p;
+    b.N = p.N - r.n1;
+    b.W = p.W + (size_t)r.n1 * p.ldw;
+    if (p.bias) b.bias = p.bias + r.n1;
+    b.out = out_at<OT, EPI>(p, 0, EPI == EPI_SWIGLU ? r.n1 / 2 : r.n1);
+    return launch_plan<OT, EPI>(b, s, false);
+  }
+  if (r.slices == 1) return launch_plan_tile<OT, EPI>(p, r.tile, s, 1);
+  if constexpr (EPI != EPI_POS) {
+    GemmArgs q = p;
+    q.out = p.split_ws;
+    q.ldo = p.N;
+    q.kslice = (p.K / BK + r.slices - 1) / r.slices * BK;
+    q.split_stride = (long)p.M * p.N;
+    const hipError_t e = launch_plan_tile<float, EPI_STORE>(q, r.tile, s, r.slices);
+    return e != hipSuccess ? e : finish_slices<OT, EPI>(p, s, r.slices);
+  }
+  return hipErrorInvalidValue;
+}
+
+// Rows to run as 256x256 tiles ahead of the rest (0: no split): with more than 16 row tiles and a
+// last round of 256x256 tiles (one workgroup per CU) that would leave part of the GPU idle, the rows
+// of whole rounds go first and the leftover rows are planned by themselves.  *us gets the estimated
+// time of both.  The results are bit-identical to one launch when the rest runs unsplit (the same K
+// order per output).  The screenshot encode (53 row tiles): QKV 4 -> 3.5 rounds, MLP up 5 -> 4.5,
+// O and down 2 -> 1.5; the 8-image MLP down (162 x 5): 4 -> 3.5.
+static int row_split_rows(const GemmArgs& p, double* us) {
   const int nm = (p.M + 255) / 256, nn = p.N / 256;
-  if (p.N % 256 || nm <= 16) return 0;
+  if (p.N % 256 || nm <= 16 || p.pos != nullptr) return 0;
   const long tiles = (long)nm * nn, full = tiles / 256;
   if (full < 1) return 0;
   const int m1 = (int)(full * 256 / nn);
   if (m1 < 1 || m1 >= nm) return 0;
-  const long rem = (long)((p.M - m1 * 256 + 127) / 128) * (p.N / 128);
-  const double split = (double)(((long)m1 * nn + 255) / 256) + (rem <= 256 ? 0.5 : 0.71 * (double)((rem + 511) / 512));
-  return split <= (double)((tiles + 255) / 256) - 0.3 ? m1 * 256 : 0;
-}
-
-// 128x128 tiles with K cut into split_slices(p) slices (when that is more than one): fp32 partials
-// in p.split_ws, then summed in slice order by split_reduce_kernel (or left for the caller to fold,
-// with p.slices_out).  *done = false when the problem runs unsplit.
-template <typename OT, int EPI>
-static hipError_t launch_slices128(const GemmArgs& p, hipStream_t s, bool* done) {
-  *done = false;
-  if constexpr (EPI == EPI_STORE || EPI == EPI_RESID) {
-    const int sl = p.vt == nullptr ? split_slices(p) : 1;
-    if (sl <= 1) return hipSuccess;
-    *done = true;
-    GemmArgs q = p;
-    q.out = p.split_ws;
-    q.ldo = p.N;
-    q.kslice = p.K / sl;
-    q.split_stride = (long)p.M * p.N;
-    q.vt = nullptr;
-    hipError_t e = launch_dma<float, EPI_STORE, 128, 128, 64, 64>(q, s, sl);
-    if (e != hipSuccess) return e;
-    if (EPI == EPI_RESID && p.slices_out != nullptr && p.bias == nullptr) {   // the caller folds them
-      *p.slices_out = sl;
-      return hipSuccess;
-    }
-    const long n4 = (long)p.M * (p.N / 4);
-    hipLaunchKernelGGL((split_reduce_kernel<OT, EPI>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, p,
-                       (const float*)p.split_ws, sl);
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  const int max_slices = p.split_ws != nullptr && p.vt == nullptr ? 16 : 1;
+  *us = tile_us(kTiles[kNumTiles - 1], (long)m1 * nn, p.K / BK, (double)p.N * p.K * 2) + 2.0 +
+        plan_gemm(p.M - m1 * 256, p.N, p.K, max_slices, p.split_ws_floats, false).us;
+  return m1 * 256;
 }
 
 template <typename TA, typename OT, int EPI>
 static hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
   if constexpr (sizeof(TA) == 2) {
     if (p.small_tiles) return launch_dma<OT, EPI, 128, 128, 64, 64>(p, s);
-    if constexpr (EPI != EPI_POS) {
-      if (const int m1 = row_split_rows(p)) {
+    double us = 1e30;
+    if (const int m1 = row_split_rows(p, &us)) {
+      if (us < plan_gemm(p.M, p.N, p.K, 1, 0, false).us) {
         GemmArgs a = p;
         a.M = m1;
         hipError_t e = launch_dma<OT, EPI, 256, 256, 64, 128>(a, s);
@@ -698,95 +949,11 @@ static hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
         b.A = reinterpret_cast<const bf16_t*>(p.A) + (size_t)m1 * p.lda;
         b.out = out_at<OT, EPI>(p, m1, 0);
         b.vt_row0 = p.vt_row0 + m1;
-        // the leftover rows are few tiles (a 1092x2408 screenshot's O and down projections: 30 of
-        // 128x128): with a long K they take K slices (its down projection: 4, 120 workgroups)
-        if (p.slices_out == nullptr) {
-          bool done = false;
-          const hipError_t e2 = launch_slices128<OT, EPI>(b, s, &done);
-          if (done || e2 != hipSuccess) return e2;
-        }
-        return launch_dma<OT, EPI, 128, 128, 64, 64>(b, s);
+        b.slices_out = nullptr;
+        return launch_plan<OT, EPI>(b, s, false);
       }
     }
-  }
-  // 256x256 tiles with 8 waves (two per SIMD, each 64x128) when there are at least two tiles per
-  // CU; otherwise 128x128 tiles with 4 waves (two workgroups per CU), with K split into slices
-  // when those tiles cannot fill the GPU (and the caller gave a workspace).  A projection that
-  // also stores V^T (p.vt) always runs as one launch: the split paths have no V^T epilogue.
-  if constexpr (sizeof(TA) == 2 && (EPI == EPI_STORE || EPI == EPI_RESID)) {
-    const long tiles256 = (long)((p.M + 255) / 256) * (p.N / 256);
-    // a very long K whose 256x256 tiles make one round of at least three quarters of the GPU
-    // (the 3.6k-token prefill's down projection: 14 x 14 tiles, K = 18944): one unsplit launch,
-    // without the split partials' traffic
-    if (p.N % 256 == 0 && p.K >= 8192 && tiles256 >= 192 && tiles256 <= 256)
-      return launch_dma<OT, EPI, 256, 256, 64, 128>(p, s);
-    // a long K whose 256x256 tiles fill under three quarters of the GPU (the 1500-token prefill's
-    // down projection: 6 x 14 tiles, K = 18944; its O projection: 6 x 14 tiles, K = 3584): K
-    // slices of 256x256 tiles that make one round of at least 224 of the 256 CUs (3 slices of
-    // 6336, 6336 and 6272, and of 1216, 1216 and 1152 there), then the fp32 partials summed in
-    // slice order
-    if (p.split_ws && p.vt == nullptr && p.N % 256 == 0 && p.K >= 3072 && tiles256 < 192) {
-      int sl = 0;
-      for (int c = 2; c <= 4 && !sl; ++c) {
-        const int kslice = (p.K / BK + c - 1) / c * BK;
-        if (tiles256 * c >= 224 && tiles256 * c <= 256 && p.K - (c - 1) * kslice >= 1024 &&
-            (size_t)c * p.M * p.N <= p.split_ws_floats)
-          sl = c;
-      }
-      if (sl) {
-        GemmArgs q = p;
-        q.out = p.split_ws;
-        q.ldo = p.N;
-        q.kslice = (p.K / BK + sl - 1) / sl * BK;
-        q.split_stride = (long)p.M * p.N;
-        q.vt = nullptr;
-        hipError_t e = launch_dma<float, EPI_STORE, 256, 256, 64, 128>(q, s, sl);
-        if (e != hipSuccess) return e;
-        if (EPI == EPI_RESID && p.slices_out != nullptr && p.bias == nullptr) {   // the caller folds them
-          *p.slices_out = sl;
-          return hipSuccess;
-        }
-        const long n4 = (long)p.M * (p.N / 4);
-        hipLaunchKernelGGL((split_reduce_kernel<OT, EPI>), dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, p,
-                           (const float*)p.split_ws, sl);
-        return hipGetLastError();
-      }
-    }
-    // 256x256 tiles that fill at least three quarters of one round of the GPU (one workgroup per
-    // CU) beat two rounds of 128x128 tiles (the 3.6k-token prefill's QKV projection: 14 x 18
-    // tiles, 157 -> 99 us; the one-image encode's MLP up projection)
-    if (p.N % 256 == 0 && tiles256 >= 192 && tiles256 < 512) return launch_dma<OT, EPI, 256, 256, 64, 128>(p, s);
-    if (!(p.N % 256 == 0 && tiles256 >= 512) && p.vt == nullptr) {
-      bool done = false;
-      const hipError_t e = launch_slices128<OT, EPI>(p, s, &done);
-      if (done || e != hipSuccess) return e;
-    }
-  }
-  if constexpr (sizeof(TA) == 2) {
-    const int nm = (p.M + 255) / 256;
-    const long tiles = (long)nm * (p.N / 256);
-    if (p.N % 256 == 0 && tiles >= 512) {
-      // few row tiles and many column tiles (the prefill's gate/up projection: 6 x 148): the
-      // columns of whole rounds of 256x256 tiles, then the rest with 128x128 tiles, so that the
-      // last round is not left mostly idle
-      const long rounds = tiles / 256;
-      const int n1 = (int)(rounds * 256 / nm) * 256;
-      if (tiles % 256 >= 32 && nm <= 16 && n1 < p.N && EPI != EPI_POS && p.vt == nullptr) {
-        GemmArgs a = p;
-        a.N = n1;
-        hipError_t e = launch_dma<OT, EPI, 256, 256, 64, 128>(a, s);
-        if (e != hipSuccess) return e;
-        GemmArgs b = p;
-        b.N = p.N - n1;
-        b.W = p.W + (size_t)n1 * p.ldw;
-        if (p.bias) b.bias = p.bias + n1;
-        b.out = out_at<OT, EPI>(p, 0, EPI == EPI_SWIGLU ? n1 / 2 : n1);
-        return launch_dma<OT, EPI, 128, 128, 64, 64>(b, s);
-      }
-      return launch_dma<OT, EPI, 256, 256, 64, 128>(p, s);
-    }
-    if (p.N % 256 == 0 && tiles >= 192) return launch_dma<OT, EPI, 256, 256, 64, 128>(p, s);
-    return launch_dma<OT, EPI, 128, 128, 64, 64>(p, s);
+    return launch_plan<OT, EPI>(p, s, true);
   }
   return launch_tile<TA, OT, EPI, 128, 128, 64, 64>(p, s);
 }

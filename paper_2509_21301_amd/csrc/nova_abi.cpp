@@ -381,27 +381,51 @@ extern "C" void nova_vit_destroy(nova_vit* v) {
 }
 
 namespace {
+// The encoder's buffers.  K-slice partials of a projection go to whatever is free around it: the MLP
+// down projection's to a..slices, the O projection's to slices and hmlp, the MLP up projection's to
+// qkv..slices, the merge's to att..hmlp (never over vt, whose key padding stays zero for the whole pass).
+// With few rows those are too small for the slices that fill the GPU (16 of M x H floats, at most 256
+// workgroups of 256x128 outputs), so `slices` adds what a..att, 2.5 M H floats in bf16, leaves missing;
+// it shrinks more slowly than those grow, so a larger batch's workspace always serves a smaller batch.
 template <typename T>
-size_t vit_ws(const nova_vit* v, int B, Carve* cv) {
+struct VitBufs {
+  T* patches;
+  float* x;        // residual stream
+  T* vt;           // V^T
+  T* a;            // normed rows
+  T* qkv;          // also the merged rows of the adapter
+  T* att;          // attention output
+  float* slices;
+  T* hmlp;         // MLP hidden
+  char* end;
+  size_t used;
+};
+
+template <typename T>
+VitBufs<T> vit_bufs(const nova_vit* v, int B, void* base) {
   const nova_vit_config& c = v->d.cfg;
   const size_t M = (size_t)B * v->npatch, H = c.hidden;
   const int skp = round_up(v->npatch, 64);
-  Carve tmp(nullptr);
-  Carve& w = cv ? *cv : tmp;
-  w.take<T>(M * v->kpad);           // patches
-  w.take<float>(M * H);             // residual stream
-  w.take<T>(M * H);                 // normed rows
-  w.take<T>(M * 3 * H);             // qkv (also the merged rows of the adapter)
-  w.take<T>((size_t)B * H * skp);   // V^T
-  w.take<T>(M * H);                 // attention output
-  w.take<T>(M * v->ip);             // MLP hidden
-  return w.used;
+  Carve w(base);
+  VitBufs<T> d;
+  d.patches = w.take<T>(M * v->kpad);
+  d.x = w.take<float>(M * H);
+  d.vt = w.take<T>((size_t)B * H * skp);
+  d.a = w.take<T>(M * H);
+  d.qkv = w.take<T>(M * 3 * H);
+  d.att = w.take<T>(M * H);
+  const size_t want = std::min<size_t>(16 * M * H, (size_t)256 * 256 * 128), have = 5 * M * H / 2;
+  d.slices = w.take<float>(sizeof(T) == 2 && want > have ? want - have : 0);
+  d.hmlp = w.take<T>(M * v->ip);
+  d.used = w.used;
+  d.end = (char*)base + w.used;
+  return d;
 }
 }  // namespace
 
 extern "C" size_t nova_vit_workspace_bytes(const nova_vit* v, int batch) {
   if (!v || batch <= 0) return 0;
-  return v->d.cfg.act == NOVA_ACT_F32 ? vit_ws<float>(v, batch, nullptr) : vit_ws<bf16_t>(v, batch, nullptr);
+  return v->d.cfg.act == NOVA_ACT_F32 ? vit_bufs<float>(v, batch, nullptr).used : vit_bufs<bf16_t>(v, batch, nullptr).used;
 }
 
 extern "C" int nova_prefetch_layer(nova_vit* v, int layer, nova_stream_t cs_in) {
@@ -434,14 +458,14 @@ int vit_encode_t(nova_vit* v, const void* pixels, int B, void* out, void* ws, hi
   const int H = c.hidden, N = v->npatch, M = B * N, hd = v->hd, heads = c.heads;
   const int gh = c.image_h / c.patch, gw = c.image_w / c.patch;
   const int skp = round_up(N, 64);
-  Carve w(ws);
-  T* patches = w.take<T>((size_t)M * v->kpad);
-  float* x = w.take<float>((size_t)M * H);
-  T* a = w.take<T>((size_t)M * H);
-  T* qkv = w.take<T>((size_t)M * 3 * H);
-  T* vt = w.take<T>((size_t)B * H * skp);
-  T* att = w.take<T>((size_t)M * H);
-  T* hmlp = w.take<T>((size_t)M * v->ip);
+  const VitBufs<T> d = vit_bufs<T>(v, B, ws);
+  T *patches = d.patches, *a = d.a, *qkv = d.qkv, *vt = d.vt, *att = d.att, *hmlp = d.hmlp;
+  float* x = d.x;
+  // K-slice partials of a projection in the free bytes from `from` up to `to`
+  auto with_slices = [](GemmArgs& p, void* from, void* to) {
+    p.split_ws = (float*)from;
+    p.split_ws_floats = ((char*)to - (char*)from) / sizeof(float);
+  };
 
   const char* emb = (const char*)v->d.embed;
   auto ew = [&](int i) { return (const bf16_t*)(emb + v->emb.off[i]); };
@@ -493,19 +517,18 @@ int vit_encode_t(nova_vit* v, const void* pixels, int B, void* out, void* ws, hi
     }
     {
       GemmArgs p{att, H, W(4), H, M, H, H, W(5), x, H, nullptr, 0};
-      // K-slice partials, where the GEMM takes them: the MLP hidden is free here
-      p.split_ws = reinterpret_cast<float*>(hmlp), p.split_ws_floats = (size_t)M * v->ip * sizeof(T) / sizeof(float);
+      with_slices(p, d.slices, d.end);
       CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_RESID, s)));
     }
     CALL(NOVA_KIND_MISC, s, nova::norm_rows<T>(x, M, H, W(6), W(7), c.eps, 1, a, H, 1, 0, 0, s));
     {
       GemmArgs p{a, H, W(8), H, M, v->ip, H, W(9), hmlp, v->ip, nullptr, 0};
+      with_slices(p, qkv, hmlp);
       CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_GELU, s)));
     }
     {
       GemmArgs p{hmlp, v->ip, W(10), v->ip, M, H, v->ip, W(11), x, H, nullptr, 0};
-      // K-slice partials in the packed QKV buffer, free until the next layer's projection
-      p.split_ws = reinterpret_cast<float*>(qkv), p.split_ws_floats = (size_t)M * 3 * H * sizeof(T) / sizeof(float);
+      with_slices(p, a, hmlp);
       CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_RESID, s)));
     }
     if (v->offload) {
@@ -525,7 +548,7 @@ int vit_encode_t(nova_vit* v, const void* pixels, int B, void* out, void* ws, hi
   CALL(NOVA_KIND_MISC, s, nova::norm_rows<T>(x, M, H, HW(0), HW(1), c.eps, 1, merged, m2 * H, c.merge, gh, gw, s));
   {
     GemmArgs p{merged, m2 * H, HW(2), m2 * H, Mo, c.out_hidden, m2 * H, HW(3), out, c.out_hidden, nullptr, 0};
-    p.split_ws = reinterpret_cast<float*>(hmlp), p.split_ws_floats = (size_t)M * v->ip * sizeof(T) / sizeof(float);
+    with_slices(p, att, d.end);
     CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_STORE, s)));
   }
   return NOVA_OK;
@@ -579,9 +602,15 @@ extern "C" size_t nova_kv_bytes(const nova_llm* m, int num_blocks) {
 }
 
 namespace {
+// K slices of a small problem's ring tiles: at most 256 workgroups of 256x128 outputs
+constexpr size_t kSliceFloats = (size_t)256 * 256 * 128;
 // Split-K partials of the prefill projections: up to 4 K slices of the widest split output.
 size_t prefill_split_floats(const nova_llm* m, int S) {
   return (size_t)4 * S * std::max<size_t>(m->d.cfg.hidden, m->qkvw);
+}
+size_t prefill_split_floats_gemm(const nova_llm* m, int S) {
+  const size_t row = (size_t)S * std::max<size_t>(m->d.cfg.hidden, m->qkvw);
+  return std::max<size_t>(4 * row, std::min<size_t>(16 * row, kSliceFloats));
 }
 
 template <typename T>
@@ -597,7 +626,7 @@ size_t prefill_ws(const nova_llm* m, int S, Carve* cv) {
   w.take<T>((size_t)S * c.n_q * c.head_dim);                     // attention out
   w.take<T>((size_t)S * m->ip);                                  // MLP hidden
   w.take<unsigned long long>(1);                                 // argmax key
-  w.take<float>(prefill_split_floats(m, S));                     // split-K partials
+  w.take<float>(prefill_split_floats_gemm(m, S));                // split-K partials
   w.take<unsigned>((size_t)c.n_q * ((S + 127) / 128));           // attention arrival counters
   return w.used;
 }
@@ -673,7 +702,7 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
   T* att = w.take<T>((size_t)S * qd);
   T* hm = w.take<T>((size_t)S * m->ip);
   unsigned long long* keys = w.take<unsigned long long>(1);
-  const size_t split_floats = prefill_split_floats(m, S);
+  const size_t split_floats = prefill_split_floats_gemm(m, S);
   float* split_ws = w.take<float>(split_floats);
   const int n_cnt = c.n_q * ((S + 127) / 128);
   unsigned* att_cnt = w.take<unsigned>((size_t)n_cnt);
@@ -717,13 +746,13 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
       nova::AttnArgs p{qkv, m->qkvw, 0, qkv + qd, m->qkvw, 0, vt, skp, att, qd, 0, S, S, c.n_q, c.n_kv, 1, 1};
       // the split-K partials are free between the QKV and O projections: the attention's key
       // ranges keep theirs there
-      p.part = split_ws, p.part_bytes = split_floats * sizeof(float), p.counters = att_cnt, p.cus = cus;
+      p.part = split_ws, p.part_bytes = prefill_split_floats(m, S) * sizeof(float), p.counters = att_cnt, p.cus = cus;
       CALL(NOVA_KIND_ATTN, s, nova::attention<T>(p, D, s));
     }
     if (int rc = resid_then_norm(with_split(GemmArgs{att, qd, W(2), qd, S, H, qd, nullptr, x, H, nullptr, 0}), W(3)))
       return rc;
     {
-      GemmArgs p{a, H, W(4), H, S, 2 * m->ip, H, nullptr, hm, m->ip, nullptr, 0};
+      const GemmArgs p = with_split(GemmArgs{a, H, W(4), H, S, 2 * m->ip, H, nullptr, hm, m->ip, nullptr, 0});
       CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_SWIGLU, s)));
     }
     {

@@ -1,0 +1,80 @@
+"""The tile plan of the encode and prefill GEMM at its edges, against the oracle: row counts around
+every tile height (ragged last tiles, a single row), K of one, two and three 64-wide steps (shorter
+than the ring of LDS stages), whole column rounds with a leftover launch, and the K-sliced GELU, SwiGLU,
+residual and store epilogues of problems with few rows."""
+import numpy as np
+import pytest
+
+from oracle import vlm
+from paper_2509_21301_amd import synth
+from tests import stage_cases as sc
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-4     # fp32 accumulation of exact bf16 products, compared norm-wise with float64
+
+
+@pytest.mark.parametrize("m,k,n", [(1, 64, 128), (31, 128, 256), (32, 192, 256), (33, 1280, 3840), (63, 1280, 1280),
+                                   (65, 640, 5120), (127, 1280, 128), (129, 3584, 4608), (200, 512, 37888),
+                                   (255, 1280, 1280), (257, 320, 5120), (511, 1280, 3840), (700, 256, 9472),
+                                   (1025, 1280, 1280), (4161, 128, 1280)])
+def test_linear_tile_edges(gpu_lib, m, k, n):
+    import torch
+    x = synth.normal((m, k), 3, f"gt_x{m}x{k}", std=1.0)
+    w = synth.normal((n, k), 3, f"gt_w{n}x{k}", std=0.05)
+    base = synth.normal((m, n), 4, f"gt_o{m}x{n}", std=1.0)
+    guard = torch.full((m + 1, n), 7.0, dtype=torch.float32, device="cuda")
+    guard[:m].copy_(torch.from_numpy(base))
+    gpu_lib.linear(gpu_lib.LINEAR_TILED, torch.from_numpy(x).cuda().to(torch.bfloat16),
+                   torch.from_numpy(w).cuda().to(torch.bfloat16), guard[:m])
+    torch.cuda.synchronize()
+    assert vlm.max_rel_err(guard[:m].cpu().numpy(), base + vlm.linear(x, w)) < TOL
+    assert bool((guard[m] == 7.0).all())          # nothing written past the last row
+
+
+# 2560-wide layers with 256-wide MLPs: few tiles and a long K, so the MLP up projections (GELU here,
+# SwiGLU below) run as K slices too; images of 4 and 40 patches, two at a time
+@pytest.mark.parametrize("h,w", [(28, 28), (56, 140)])
+def test_vit_few_rows(gpu_lib, h, w):
+    import torch
+    cfg = synth.VitConfig(hidden=2560, heads=32, mlp=256, layers=2, patch=14, merge=2, out_hidden=256, image_h=h,
+                          image_w=w, name=f"vit_few_{h}x{w}")
+    wt = synth.vit_weights(cfg, seed=8)
+    imgs = synth.image(2, h, w, seed=3)
+    out = gpu_lib.Vit(cfg, wt).encode(torch.from_numpy(imgs).cuda().to(torch.bfloat16)).float().cpu().numpy()
+    for i in range(2):
+        assert vlm.max_rel_err(out[i], vlm.vit_encode(imgs[i], wt, cfg)) < sc.TOL_BF16, f"image {i}"
+
+
+# patch embedding with its position table (3456 patches x 1280: more tiles than one round of any tile)
+def test_vit_patch_embed_positions(gpu_lib):
+    import torch
+    cfg = synth.VitConfig(hidden=1280, heads=16, mlp=256, layers=0, patch=4, merge=2, out_hidden=256, image_h=192,
+                          image_w=288, name="vit_pos")
+    for batch in (1, 4):
+        wt = synth.vit_weights(cfg, seed=8)
+        imgs = synth.image(batch, cfg.image_h, cfg.image_w, seed=3)
+        out = gpu_lib.Vit(cfg, wt).encode(torch.from_numpy(imgs).cuda().to(torch.bfloat16)).float().cpu().numpy()
+        for i in range(batch):
+            assert vlm.max_rel_err(out[i], vlm.vit_encode(imgs[i], wt, cfg)) < sc.TOL_BF16, f"image {i}"
+
+
+@pytest.mark.parametrize("n_vis,n_text", [(0, 1), (3, 30), (0, 33), (70, 60)])
+def test_prefill_few_rows(gpu_lib, n_vis, n_text):
+    import torch
+    cfg = synth.LlmConfig(hidden=2560, n_q=20, n_kv=4, head_dim=128, inter=200, vocab=16384, layers=2, name="llm_few")
+    wt = synth.llm_weights(cfg, seed=6)
+    vis = synth.vision_embeds(n_vis, cfg.hidden) if n_vis else np.zeros((0, cfg.hidden), np.float32)
+    ids = synth.text_ids(n_text, cfg.vocab)
+    table, pool = synth.block_tables([n_vis + n_text], cfg.block, seed=5)
+    kref = vlm.PagedKV(cfg.layers, pool, cfg.n_kv, cfg.block, cfg.head_dim)
+    ref, _ = vlm.llm_prefill(vis, ids, wt, cfg, kv=kref, table=table[0])
+    llm = gpu_lib.Llm(cfg, wt)
+    kv = gpu_lib.KvPool(llm, pool)
+    logits = torch.empty(cfg.vocab, dtype=torch.float32, device="cuda")
+    llm.prefill(torch.from_numpy(vis).cuda().to(torch.bfloat16) if n_vis else None, torch.from_numpy(ids).cuda(),
+                torch.from_numpy(table[0]).cuda(), kv, logits=logits)
+    torch.cuda.synchronize()
+    assert vlm.max_rel_err(logits.cpu().numpy(), ref) < sc.TOL_BF16
+    ek, ev = sc.kv_errors(kref.k, kref.v, kv.k5.float().cpu().numpy(), kv.v5.float().cpu().numpy())
+    assert ek < sc.TOL_BF16 and ev < sc.TOL_BF16
