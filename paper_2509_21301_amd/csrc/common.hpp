@@ -55,6 +55,22 @@ NOVA_DEV f32x16 mfma32(const Frag8& a, const Frag8& b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
 }
 
+// One 16-byte-per-lane LDS-DMA load (lane l's 16 bytes from g land at lds_addr + 16 l) written as
+// inline assembly, to the LDS byte address lds_addr
+// (wave-uniform, passed in M0).  The compiler does not track it: a fragment read that follows it
+// in program order is not made to wait for it, so the caller orders DMA and reads itself with
+// s_waitcnt and barriers.
+NOVA_DEV void lds_dma16_untracked(const bf16_t* g, uint32_t lds_addr) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(g)
+               : "memory");
+}
+NOVA_DEV uint32_t lds_addr_of(const void* p) {
+  return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) char*)p);
+}
+
+// s_waitcnt operand: at most n vector memory instructions outstanding, every LDS read returned.
+__host__ __device__ constexpr int wait_vm_lds(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
+
 NOVA_DEV float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);

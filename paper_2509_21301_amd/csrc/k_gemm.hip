@@ -331,18 +331,6 @@ __device__ __forceinline__ void lds_dma16(const bf16_t* g, bf16_t* l_base) {
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)l_base, 16, 0, 0);
 }
 
-// The same 16-byte LDS-DMA load written as inline assembly, to the LDS byte address lds_addr
-// (wave-uniform, passed in M0).  The compiler does not track it: a fragment read that follows it
-// in program order is not made to wait for it, so the caller orders DMA and reads itself with
-// s_waitcnt and barriers.
-__device__ __forceinline__ void lds_dma16_untracked(const bf16_t* g, uint32_t lds_addr) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"{m0}"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(g)
-               : "memory");
-}
-__device__ __forceinline__ uint32_t lds_addr_of(const void* p) {
-  return (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) char*)p);
-}
-
 template <typename OT, int EPI, int BM, int BN, int WM, int WN>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_dma_kernel(GemmArgs p) {
   constexpr int TM = WM / 16, TN = WN / 16;
@@ -638,18 +626,16 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_ring_kernel(G
     rs = rs + 1 == NST ? 0 : rs + 1;
     ws = ws + 1 == NST ? 0 : ws + 1;
   };
-  // s_waitcnt operand: at most n DMA instructions outstanding, and every fragment read returned
-  constexpr auto vm = [](int n) constexpr { return 0x0070 | (n & 15) | ((n >> 4) << 14); };
   int kt = 0;
   for (; kt + NST - 2 < nk; ++kt) {
-    __builtin_amdgcn_s_waitcnt(vm((NST - 2) * IT));
+    __builtin_amdgcn_s_waitcnt(wait_vm_lds((NST - 2) * IT));
     step(kt + NST - 1 < nk ? kt + NST - 1 : -1);
   }
   auto last = [&](auto younger) {                    // one of the last steps, `younger` stages behind it
     constexpr int J = decltype(younger)::value;
     if constexpr (J <= NST - 3) {
       if (nk > J) {
-        __builtin_amdgcn_s_waitcnt(vm(J * IT));
+        __builtin_amdgcn_s_waitcnt(wait_vm_lds(J * IT));
         step(-1);
       }
     }

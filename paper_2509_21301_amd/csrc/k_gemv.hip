@@ -61,8 +61,22 @@ __device__ __forceinline__ int swz(int row, int piece) { return row * GV_KC + 8 
 // TA: activation type of X (bf16, or fp32 for the exact mode whose operands are split into bf16
 // hi + lo).  NSCALE: X holds x * gain of a folded RMSNorm; output columns are scaled by the row's
 // rsqrt(mean x^2 + eps), from the producer's per-tile sums of squares.
-template <typename TA, typename OT, int NB, int EPI, bool DIRECT, bool NSCALE>
-__global__ void __launch_bounds__(256) gemv_kernel(GemvArgs p, int kc) {
+// RING (bf16): X and W come through a ring of LDS stages filled by LDS-DMA, 64 wide along K, instead of
+// through registers.  With more than 16 batch rows the register path moves 144 KB through LDS per 32 KB
+// of weights (write and read of W, write and four reads of X) and holds two chunks ahead in 160
+// registers; the ring moves 96 KB, needs no staging registers and keeps 32 KB of weights in flight per
+// workgroup.  ROWS: weight rows per workgroup.  128 rows halve the X traffic per weight; they pay where
+// they still make two rounds of workgroups (the LM head, one column group or two), and lose where they
+// do not (gate/up at batch 32: 60 us with 592 workgroups of 64 rows, 65 us with 296 of 128).
+// At batch 32: gate/up 61.9 -> 60.0 us, QKV 12.7 -> 11.6, LM head 231.9 -> 209 us; LM head at batch 8
+// 195 -> 190 us, at batch 1 182 -> 181 us.
+constexpr int GV_BK = 64;              // ring: K per stage
+
+template <typename TA, typename OT, int NB, int EPI, bool DIRECT, bool NSCALE, bool RING, int ROWS>
+__global__ void __launch_bounds__(ROWS * 4) gemv_kernel(GemvArgs p, int kc) {
+  static_assert(ROWS == GV_ROWS || (RING && EPI != EPI_RESID), "wide workgroups: ring, no residual epilogue");
+  constexpr int NWV = ROWS / GV_RW;                       // waves
+  constexpr int GV_NST = ROWS == GV_ROWS ? 5 : 3;         // ring stages: 60 KB, two workgroups per CU
   using TX = TA;
   constexpr bool F32X = sizeof(TA) == 4;                  // X fp32, operands split into bf16 hi + lo
   constexpr int XROWS = 16 * NB;                          // batch rows held (B padded)
@@ -70,142 +84,198 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs p, int kc) {
   constexpr int XSLOT = XROWS * GV_KC * (F32X ? 2 : 1);   // bf16 per slot (fp32 mode: hi, lo)
   constexpr int XPT = XROWS / 8;                          // 16-byte X pieces per thread per chunk
   constexpr int XL = F32X ? 2 * XPT : XPT;                // X loads per thread per chunk
-  __shared__ __align__(16) bf16_t wt[4][GV_RW * GV_KC];
-  __shared__ __align__(16) bf16_t xs[XR * XSLOT];
+  constexpr int STAGE = (XROWS + ROWS) * GV_BK;           // ring: X rows, then the weight rows
+  __shared__ __align__(16) bf16_t wt[4][RING ? 8 : GV_RW * GV_KC];
+  __shared__ __align__(16) bf16_t xs[RING ? GV_NST * STAGE : XR * XSLOT];
   __shared__ float red[EPI == EPI_RESID ? 4 : 1][32];     // per-wave row statistics (residual producers)
   __shared__ float rstd_s[NSCALE ? 32 : 1];                // per-row RMSNorm scale (normalising consumers)
-  __shared__ unsigned long long am_s[EPI == EPI_ARGMAX ? 4 : 1][16];   // per-wave argmax keys
+  __shared__ unsigned long long am_s[EPI == EPI_ARGMAX ? NWV : 1][16];   // per-wave argmax keys
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n_base = blockIdx.x * GV_ROWS + wave * GV_RW;
+  const int n_base = blockIdx.x * ROWS + wave * GV_RW;
   const int split = blockIdx.y;
   const int k_begin = split * kc, k_end = min(k_begin + kc, p.K);
-  const int nchunks = (k_end - k_begin) / GV_KC;
   const int n = lane & 15, g = lane >> 4;          // MFMA operand row and k group
   const int h = lane >> 5, pc = lane & 31;         // load row within a pair, piece
-
-  // weight load i of a chunk: rows 2i + h, piece pc (lanes 0-31 and 32-63 each read one row)
-  const bf16_t* wsrc = p.W + (size_t)(n_base + h) * p.ldw + k_begin + 8 * pc;
-  typedef u32x4 WBuf[8];
-  auto load_w = [&](int c, WBuf& w) {
-    const bf16_t* src = wsrc + (size_t)min(c, nchunks - 1) * GV_KC;   // tail: re-read the last chunk
-#pragma unroll
-    for (int i = 0; i < 8; ++i) w[i] = *reinterpret_cast<const u32x4*>(src + (size_t)(2 * i) * p.ldw);
-  };
-  // X piece q of a chunk for this thread: batch row tid / 32 + 8q (clamped to B-1: those rows
-  // only feed output columns that are never stored), piece tid % 32
-  const TX* X = reinterpret_cast<const TX*>(p.X);
-  typedef u32x4 XBuf[XL];
-  auto load_x = [&](int c, XBuf& x) {
-    const int k = k_begin + min(c, nchunks - 1) * GV_KC + 8 * pc;
-#pragma unroll
-    for (int q = 0; q < XPT; ++q) {
-      const TX* src = X + (size_t)min((tid >> 5) + 8 * q, p.B - 1) * p.ldx + k;
-      if constexpr (F32X) {
-        x[2 * q] = *reinterpret_cast<const u32x4*>(src);
-        x[2 * q + 1] = *reinterpret_cast<const u32x4*>(src + 4);
-      } else {
-        x[q] = *reinterpret_cast<const u32x4*>(src);
-      }
-    }
-  };
-  auto store_x = [&](const XBuf& x, int slot) {
-    bf16_t* dst = xs + slot * XSLOT;
-#pragma unroll
-    for (int q = 0; q < XPT; ++q) {
-      const int r = (tid >> 5) + 8 * q;
-      if constexpr (F32X) {
-        float x8[8];
-        *reinterpret_cast<u32x4*>(x8) = x[2 * q];
-        *reinterpret_cast<u32x4*>(x8 + 4) = x[2 * q + 1];
-        Frag8 hi, lo;
-        split8(x8, hi, lo);
-        *reinterpret_cast<Frag8*>(dst + swz(r, pc)) = hi;
-        *reinterpret_cast<Frag8*>(dst + XROWS * GV_KC + swz(r, pc)) = lo;
-      } else {
-        *reinterpret_cast<u32x4*>(dst + swz(r, pc)) = x[q];
-      }
-    }
-  };
 
   f32x4 acc[NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16_t* tw = wt[wave];
-
-  // one chunk: weights through the wave's tile into operand layout, then MFMAs against the X slot;
-  // MFMA u takes piece 4u + g of row n from both operands
-  auto compute = [&](int c, const WBuf& w) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(tw + swz(2 * i + h, pc)) = w[i];
-    // a wave's LDS operations execute in order; only the compiler has to be kept from moving
-    // the reads above the writes (or the next chunk's writes above these reads)
-    asm volatile("" ::: "memory");
-    const bf16_t* xb = xs + (c % XR) * XSLOT;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const Frag8 wf = *reinterpret_cast<const Frag8*>(tw + swz(n, 4 * u + g));
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const Frag8 xf = *reinterpret_cast<const Frag8*>(xb + swz(16 * j + n, 4 * u + g));
-        acc[j] = mfma16(wf, xf, acc[j]);
-        if constexpr (F32X) {
-          const Frag8 xl = *reinterpret_cast<const Frag8*>(xb + XROWS * GV_KC + swz(16 * j + n, 4 * u + g));
-          acc[j] = mfma16(wf, xl, acc[j]);
-        }
-      }
-    }
-    asm volatile("" ::: "memory");
-  };
-  // compute chunk c, then publish X(c+1) in its ring slot (with one slot, only after every wave
-  // is done with chunk c); the barrier makes it visible and frees the other slot
-  auto step = [&](int c, const WBuf& w, const XBuf& xnext) {
-    compute(c, w);
-    if (c + 1 < nchunks) {
-      if constexpr (XR == 1) __syncthreads();
-      store_x(xnext, (c + 1) % XR);
-    }
-    __syncthreads();
-  };
-
-  // loads are unconditional (clamped at the tail) and issued in consumption order, so that the
-  // wait before each use covers only its own chunk
   // the row statistic first (ahead of the weight stream in the in-order load counter): wave w
-  // takes batch rows w, w + 4, ...; lane t holds tile part t (<= 64 parts), summed by a
+  // takes batch rows w, w + NWV, ...; lane t holds tile part t (<= 64 parts), summed by a
   // fixed-order butterfly
-  float ssv[NSCALE ? (16 * NB + 3) / 4 : 1];
+  constexpr int SPW = (16 * NB + NWV - 1) / NWV;           // statistics per wave
+  float ssv[NSCALE ? SPW : 1];
   if constexpr (NSCALE) {
 #pragma unroll
-    for (int i = 0; i < (16 * NB + 3) / 4; ++i) {
-      const int b = min(wave + 4 * i, p.B - 1);
+    for (int i = 0; i < SPW; ++i) {
+      const int b = min(wave + NWV * i, p.B - 1);
       ssv[i] = lane < p.ss_parts ? p.ss_in[(size_t)lane * p.B + b] : 0.f;
     }
   }
-  WBuf w0, w1, w2;
-  XBuf x0, x1, x2;
-  load_x(0, x0);
-  load_w(0, w0);
-  load_x(1, x1);
-  load_w(1, w1);
-  if constexpr (NSCALE) {
+  auto row_stats = [&]() {
+    if constexpr (NSCALE) {
 #pragma unroll
-    for (int i = 0; i < (16 * NB + 3) / 4; ++i) {
-      const float ss = wave_sum(ssv[i]);
-      if (lane == 0 && wave + 4 * i < p.B) rstd_s[wave + 4 * i] = rsqrtf(ss / p.K + p.eps);
+      for (int i = 0; i < SPW; ++i) {
+        const float ss = wave_sum(ssv[i]);
+        if (lane == 0 && wave + NWV * i < p.B) rstd_s[wave + NWV * i] = rsqrtf(ss / p.K + p.eps);
+      }
     }
-  }
-  store_x(x0, 0);
-  __syncthreads();
-  for (int c = 0; c < nchunks; c += 3) {
-    load_x(c + 2, x2);
-    load_w(c + 2, w2);
-    step(c, w0, x1);
-    load_x(c + 3, x0);
-    load_w(c + 3, w0);
-    if (c + 1 < nchunks) step(c + 1, w1, x2);
-    load_x(c + 4, x1);
-    load_w(c + 4, w1);
-    if (c + 2 < nchunks) step(c + 2, w2, x0);
+  };
+  if constexpr (RING) {
+    static_assert(!F32X, "bf16");
+    // DMA instruction q (dealt to wave q % NWV) fills the stage's rows 8q .. 8q + 7: lane l row 8q + l / 8,
+    // slot l % 8 with piece (l % 8) ^ (row / 2 % 8)
+    constexpr int NQ = (XROWS + ROWS) / 8, IT = (NQ + NWV - 1) / NWV, REM = NQ - (IT - 1) * NWV;
+    const bool more = __builtin_amdgcn_readfirstlane(wave) < REM;   // this wave has IT instructions, else IT - 1
+    const bf16_t* src[IT];
+#pragma unroll
+    for (int t = 0; t < IT; ++t) {
+      const int r = min(wave + NWV * t, NQ - 1) * 8 + (lane >> 3), k = k_begin + 8 * ((lane & 7) ^ ((r >> 1) & 7));
+      src[t] = r < XROWS ? reinterpret_cast<const bf16_t*>(p.X) + (size_t)min(r, p.B - 1) * p.ldx + k
+                         : p.W + (size_t)(blockIdx.x * ROWS + r - XROWS) * p.ldw + k;
+    }
+    const uint32_t lbase = lds_addr_of(xs) + (uint32_t)(wave * 8 * GV_BK) * 2u;
+    auto dma = [&](int kt, int stage) {
+#pragma unroll
+      for (int t = 0; t < IT; ++t)
+        if (t + 1 < IT || more)
+          lds_dma16_untracked(src[t] + kt * GV_BK, lbase + (uint32_t)(stage * STAGE + t * NWV * 8 * GV_BK) * 2u);
+    };
+    const int nk = (k_end - k_begin) / GV_BK;        // a multiple of 4, so at least GV_NST - 1
+    const int off0 = n * GV_BK + 8 * (g ^ ((n >> 1) & 7)), off1 = n * GV_BK + 8 * ((g + 4) ^ ((n >> 1) & 7));
+#pragma unroll
+    for (int st = 0; st < GV_NST - 1; ++st) dma(st, st);
+    int rs = 0, ws = GV_NST - 1;                     // stage read, stage refilled
+    for (int kt = 0; kt < nk; ++kt) {
+      // this wave's part of stage kt has landed; the barrier publishes it and frees stage kt - 1
+      if (kt + GV_NST - 2 >= nk) __builtin_amdgcn_s_waitcnt(wait_vm_lds(0));
+      else if (more) __builtin_amdgcn_s_waitcnt(wait_vm_lds((GV_NST - 2) * IT));
+      else __builtin_amdgcn_s_waitcnt(wait_vm_lds((GV_NST - 2) * (IT - 1)));
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (kt + GV_NST - 1 < nk) dma(kt + GV_NST - 1, ws);
+      const bf16_t* xb = xs + rs * STAGE;
+      const bf16_t* wb = xb + (XROWS + wave * GV_RW) * GV_BK;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const Frag8 wf = *reinterpret_cast<const Frag8*>(wb + (u ? off1 : off0));
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          acc[j] = mfma16(wf, *reinterpret_cast<const Frag8*>(xb + j * 16 * GV_BK + (u ? off1 : off0)), acc[j]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      rs = rs + 1 == GV_NST ? 0 : rs + 1;
+      ws = ws + 1 == GV_NST ? 0 : ws + 1;
+    }
+    row_stats();
+    __syncthreads();
+  } else {
+    const int nchunks = (k_end - k_begin) / GV_KC;
+    // weight load i of a chunk: rows 2i + h, piece pc (lanes 0-31 and 32-63 each read one row)
+    const bf16_t* wsrc = p.W + (size_t)(n_base + h) * p.ldw + k_begin + 8 * pc;
+    typedef u32x4 WBuf[8];
+    auto load_w = [&](int c, WBuf& w) {
+      const bf16_t* src = wsrc + (size_t)min(c, nchunks - 1) * GV_KC;   // tail: re-read the last chunk
+#pragma unroll
+      for (int i = 0; i < 8; ++i) w[i] = *reinterpret_cast<const u32x4*>(src + (size_t)(2 * i) * p.ldw);
+    };
+    // X piece q of a chunk for this thread: batch row tid / 32 + 8q (clamped to B-1: those rows
+    // only feed output columns that are never stored), piece tid % 32
+    const TX* X = reinterpret_cast<const TX*>(p.X);
+    typedef u32x4 XBuf[XL];
+    auto load_x = [&](int c, XBuf& x) {
+      const int k = k_begin + min(c, nchunks - 1) * GV_KC + 8 * pc;
+#pragma unroll
+      for (int q = 0; q < XPT; ++q) {
+        const TX* src = X + (size_t)min((tid >> 5) + 8 * q, p.B - 1) * p.ldx + k;
+        if constexpr (F32X) {
+          x[2 * q] = *reinterpret_cast<const u32x4*>(src);
+          x[2 * q + 1] = *reinterpret_cast<const u32x4*>(src + 4);
+        } else {
+          x[q] = *reinterpret_cast<const u32x4*>(src);
+        }
+      }
+    };
+    auto store_x = [&](const XBuf& x, int slot) {
+      bf16_t* dst = xs + slot * XSLOT;
+#pragma unroll
+      for (int q = 0; q < XPT; ++q) {
+        const int r = (tid >> 5) + 8 * q;
+        if constexpr (F32X) {
+          float x8[8];
+          *reinterpret_cast<u32x4*>(x8) = x[2 * q];
+          *reinterpret_cast<u32x4*>(x8 + 4) = x[2 * q + 1];
+          Frag8 hi, lo;
+          split8(x8, hi, lo);
+          *reinterpret_cast<Frag8*>(dst + swz(r, pc)) = hi;
+          *reinterpret_cast<Frag8*>(dst + XROWS * GV_KC + swz(r, pc)) = lo;
+        } else {
+          *reinterpret_cast<u32x4*>(dst + swz(r, pc)) = x[q];
+        }
+      }
+    };
+
+    bf16_t* tw = wt[wave];
+
+    // one chunk: weights through the wave's tile into operand layout, then MFMAs against the X slot;
+    // MFMA u takes piece 4u + g of row n from both operands
+    auto compute = [&](int c, const WBuf& w) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(tw + swz(2 * i + h, pc)) = w[i];
+      // a wave's LDS operations execute in order; only the compiler has to be kept from moving
+      // the reads above the writes (or the next chunk's writes above these reads)
+      asm volatile("" ::: "memory");
+      const bf16_t* xb = xs + (c % XR) * XSLOT;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const Frag8 wf = *reinterpret_cast<const Frag8*>(tw + swz(n, 4 * u + g));
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          const Frag8 xf = *reinterpret_cast<const Frag8*>(xb + swz(16 * j + n, 4 * u + g));
+          acc[j] = mfma16(wf, xf, acc[j]);
+          if constexpr (F32X) {
+            const Frag8 xl = *reinterpret_cast<const Frag8*>(xb + XROWS * GV_KC + swz(16 * j + n, 4 * u + g));
+            acc[j] = mfma16(wf, xl, acc[j]);
+          }
+        }
+      }
+      asm volatile("" ::: "memory");
+    };
+    // compute chunk c, then publish X(c+1) in its ring slot (with one slot, only after every wave
+    // is done with chunk c); the barrier makes it visible and frees the other slot
+    auto step = [&](int c, const WBuf& w, const XBuf& xnext) {
+      compute(c, w);
+      if (c + 1 < nchunks) {
+        if constexpr (XR == 1) __syncthreads();
+        store_x(xnext, (c + 1) % XR);
+      }
+      __syncthreads();
+    };
+
+    // loads are unconditional (clamped at the tail) and issued in consumption order, so that the
+    // wait before each use covers only its own chunk
+    WBuf w0, w1, w2;
+    XBuf x0, x1, x2;
+    load_x(0, x0);
+    load_w(0, w0);
+    load_x(1, x1);
+    load_w(1, w1);
+    row_stats();
+    store_x(x0, 0);
+    __syncthreads();
+    for (int c = 0; c < nchunks; c += 3) {
+      load_x(c + 2, x2);
+      load_w(c + 2, w2);
+      step(c, w0, x1);
+      load_x(c + 3, x0);
+      load_w(c + 3, w0);
+      if (c + 1 < nchunks) step(c + 1, w1, x2);
+      load_x(c + 4, x1);
+      load_w(c + 4, w1);
+      if (c + 2 < nchunks) step(c + 2, w2, x0);
+    }
   }
 
   // lane holds D[n = 4*(lane/16) + r][b = lane%16] of each 16x16 tile
@@ -240,7 +310,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs p, int kc) {
         const unsigned long long other = __shfl_xor(key, o, 64);
         key = other > key ? other : key;
       }
-      // the workgroup's 4 waves combine through LDS, and one lane per row merges the result only
+      // the workgroup's waves combine through LDS, and one lane per row merges the result only
       // if it beats the row's best so far (which only grows, so a stale read merely costs an
       // extra atomic): some 2400 workgroups of the LM head would otherwise queue 4 atomics each
       // on the same address (a fifth of the head's time)
@@ -249,7 +319,7 @@ __global__ void __launch_bounds__(256) gemv_kernel(GemvArgs p, int kc) {
       if (wave == 0 && lane < 16 && b < p.B) {
         unsigned long long k = am_s[0][lane];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) k = am_s[w][lane] > k ? am_s[w][lane] : k;
+        for (int w = 1; w < NWV; ++w) k = am_s[w][lane] > k ? am_s[w][lane] : k;
         if (k > __hip_atomic_load(p.argmax_keys + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
           atomicMax(p.argmax_keys + b, k);
       }
@@ -409,17 +479,24 @@ __global__ void gemv_reduce(GemvArgs p, int splits) {
 
 template <typename TA, typename OT, int NB, int EPI, bool NSCALE>
 static hipError_t gemv_launch(const GemvArgs& p, hipStream_t s) {
-  constexpr bool F32X = sizeof(TA) == 4;
+  constexpr bool F32X = sizeof(TA) == 4, RING = NB == 2 && !F32X;
   const int splits = gemv_splits(p.N, p.K, p.B, F32X, p.cus);
   const int chunks = p.K / GV_KC;
   const int kc = (chunks + splits - 1) / splits * GV_KC;
   dim3 grid(p.N / GV_ROWS, splits);
+  if constexpr (!F32X && EPI != EPI_RESID) {
+    // 128-row workgroups while they make at least two rounds of two per CU
+    if (splits == 1 && p.N % 128 == 0 && p.N / 128 >= 4 * p.cus) {
+      hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, true, NSCALE, true, 128>), dim3(p.N / 128), dim3(512), 0, s, p, kc);
+      return hipGetLastError();
+    }
+  }
   if (splits == 1) {
-    hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, true, NSCALE>), grid, dim3(256), 0, s, p, kc);
+    hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, true, NSCALE, RING, GV_ROWS>), grid, dim3(256), 0, s, p, kc);
     return hipGetLastError();
   }
   if (!p.partial || (EPI == EPI_RESID && p.ss_out != nullptr && p.counters == nullptr)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, false, NSCALE>), grid, dim3(256), 0, s, p, kc);
+  hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, false, NSCALE, RING, GV_ROWS>), grid, dim3(256), 0, s, p, kc);
   hipError_t e = hipGetLastError();
   // out == null (except for the argmax, whose logits are optional): the caller reduces the
   // partials; a residual producer with tile counters has folded them in already

@@ -78,3 +78,43 @@ def test_prefill_few_rows(gpu_lib, n_vis, n_text):
     assert vlm.max_rel_err(logits.cpu().numpy(), ref) < sc.TOL_BF16
     ek, ev = sc.kv_errors(kref.k, kref.v, kv.k5.float().cpu().numpy(), kv.v5.float().cpu().numpy())
     assert ek < sc.TOL_BF16 and ev < sc.TOL_BF16
+
+
+@pytest.mark.parametrize("m,k,n", [(17, 256, 16384), (32, 768, 16384)])
+def test_thin_linear_ring(gpu_lib, m, k, n):
+    import torch
+    x = synth.normal((m, k), 5, f"gt_x{m}x{k}", std=1.0)
+    w = synth.normal((n, k), 5, f"gt_w{n}x{k}", std=0.05)
+    out = torch.ones((m, n), dtype=torch.float32, device="cuda")
+    gpu_lib.linear(gpu_lib.LINEAR_THIN, torch.from_numpy(x).cuda().to(torch.bfloat16),
+                   torch.from_numpy(w).cuda().to(torch.bfloat16), out)
+    torch.cuda.synchronize()
+    assert vlm.max_rel_err(out.cpu().numpy(), 1.0 + vlm.linear(x, w)) < TOL
+
+
+# a head of 132,096 rows: the LM head's 128-row workgroups, one and two column groups, partly filled
+@pytest.mark.parametrize("bsz", [1, 16, 17, 32])
+def test_decode_wide_head(gpu_lib, bsz):
+    import torch
+    cfg = synth.LlmConfig(hidden=256, n_q=4, n_kv=2, head_dim=64, inter=688, vocab=132096, layers=1, name="llm_head")
+    wt = synth.llm_weights(cfg, seed=2)
+    ctx = [5 + 3 * b for b in range(bsz)]
+    tables, pool = synth.block_tables([c + 1 for c in ctx], cfg.block, seed=9)
+    rng = np.random.default_rng(3)
+    kref = vlm.PagedKV(cfg.layers, pool, cfg.n_kv, cfg.block, cfg.head_dim)
+    kref.k[:] = synth.bf16_round(rng.standard_normal(kref.k.shape, dtype=np.float32))
+    kref.v[:] = synth.bf16_round(rng.standard_normal(kref.v.shape, dtype=np.float32))
+    llm = gpu_lib.Llm(cfg, wt)
+    kv = gpu_lib.KvPool(llm, pool)
+    kv.k5.copy_(torch.from_numpy(kref.k.astype(np.float32)).to(torch.bfloat16))
+    kv.v5.copy_(torch.from_numpy(np.swapaxes(kref.v, -1, -2).astype(np.float32)).to(torch.bfloat16))
+    ids, pos = synth.text_ids(bsz, cfg.vocab, seed=12), np.array(ctx, np.int32)
+    logits = torch.full((bsz, cfg.vocab), float("nan"), dtype=torch.float32, device="cuda")
+    nxt = llm.decode(torch.from_numpy(ids).cuda(), torch.from_numpy(pos).cuda(), torch.from_numpy(tables).cuda(), kv,
+                     max_ctx=max(ctx) + 1, logits=logits)
+    torch.cuda.synchronize()
+    ref, _ = vlm.llm_decode_step(ids, pos, tables, kref, wt, cfg)
+    got = logits.cpu().numpy()
+    for b in range(bsz):
+        assert vlm.max_rel_err(got[b], ref[b]) < sc.TOL_BF16, f"seq {b}"
+    assert np.array_equal(nxt.cpu().numpy(), np.argmax(got, axis=1))      # the fused argmax, lowest id on ties
