@@ -320,6 +320,89 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_kernel(GemmAr
   gemm_epilogue<OT, EPI, WM, WN>(p, acc, reinterpret_cast<float*>(smem), wave, lane, m0 + wm * WM, n0 + wn * WN);
 }
 
+// fp32 activations, few output tiles (exact mode): 32x64 tiles of 4 waves, the operands of the next 4 K
+// steps held in registers.  The 128x128 kernel above is bound by latency there (about 2 us per K step:
+// each waits for loads issued one step earlier, on a handful of workgroups); the sums run in the same
+// order, so the results are the same bits.  96 rows of the 256-wide decoder: QKV 11.0 -> 4.7 us, the
+// residual projections 24.8 -> 6.6 us.
+template <int EPI>
+__global__ void __launch_bounds__(256) gemm_f32_small_kernel(GemmArgs p) {
+  constexpr int BM = 32, BN = 64, WM = 16, WN = 32, TN = WN / 16, AHEAD = 4;
+  constexpr int STAGE = (2 * BM + BN) * LDK;           // bf16: A hi, A lo, W
+  __shared__ __align__(16) bf16_t lds[2 * STAGE];
+  static_assert(4 * 16 * (WN + 4) * 4 <= sizeof(lds), "epilogue scratch exceeds the stages");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+  const int nm = (p.M + BM - 1) / BM;
+  const int m0 = (int)(blockIdx.x % nm) * BM, n0 = (int)(blockIdx.x / nm) * BN;
+  // two 16-byte pieces of A (4 floats each) and two of W (8 bf16 each) per thread and step; rows past M
+  // are clamped (they feed only output rows that are never stored)
+  const float* asrc[2];
+  const bf16_t* bsrc[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int c = tid + 256 * i;
+    asrc[i] = reinterpret_cast<const float*>(p.A) + (size_t)min(m0 + (c >> 4), p.M - 1) * p.lda + (c & 15) * 4;
+    bsrc[i] = p.W + (size_t)(n0 + (c >> 3)) * p.ldw + (c & 7) * 8;
+  }
+  u32x4 ra[AHEAD][2], rb[AHEAD][2];
+  const int nk = p.K / BK;
+  auto load = [&](int kt, int slot) {
+    const int k = min(kt, nk - 1) * BK;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      ra[slot][i] = *reinterpret_cast<const u32x4*>(asrc[i] + k);
+      rb[slot][i] = *reinterpret_cast<const u32x4*>(bsrc[i] + k);
+    }
+  };
+  f32x4 acc[1][TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) acc[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int fr = lane & 15, fk = (lane >> 4) * 8;
+  auto step = [&](int kt, int slot) {
+    bf16_t* a = lds + (kt & 1) * STAGE;
+    bf16_t* b = a + 2 * BM * LDK;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = tid + 256 * i;
+      const int ao = (c >> 4) * LDK + (c & 15) * 4;
+      float x[4], l[4];
+      bf16_t h[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        x[j] = __uint_as_float(ra[slot][i][j]);
+        h[j] = f2bf(x[j]);
+        l[j] = x[j] - bf2f(h[j]);
+      }
+      *reinterpret_cast<uint2*>(a + ao) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+      *reinterpret_cast<uint2*>(a + BM * LDK + ao) = make_uint2(pack2(l[0], l[1]), pack2(l[2], l[3]));
+      *reinterpret_cast<u32x4*>(b + (c >> 3) * LDK + (c & 7) * 8) = rb[slot][i];
+    }
+    load(kt + AHEAD, slot);
+    __syncthreads();         // publishes this step's stage; the other stage's readers are past it
+#pragma unroll
+    for (int kk = 0; kk < BK; kk += 32) {
+      const Frag8 hi = *reinterpret_cast<const Frag8*>(a + (wm * WM + fr) * LDK + kk + fk);
+      const Frag8 lo = *reinterpret_cast<const Frag8*>(a + (BM + wm * WM + fr) * LDK + kk + fk);
+      Frag8 fb[TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const Frag8*>(b + (wn * WN + j * 16 + fr) * LDK + kk + fk);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[0][j] = mfma16(hi, fb[j], acc[0][j]);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[0][j] = mfma16(lo, fb[j], acc[0][j]);
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < AHEAD; ++t) load(t, t);
+  for (int kt = 0; kt < nk; kt += AHEAD) {
+#pragma unroll
+    for (int t = 0; t < AHEAD; ++t)
+      if (kt + t < nk) step(kt + t, t);
+  }
+  __syncthreads();
+  gemm_epilogue<float, EPI, WM, WN>(p, acc, reinterpret_cast<float*>(lds), wave, lane, m0 + wm * WM, n0 + wn * WN);
+}
+
 // bf16 activations: both tiles go global -> LDS directly (16-byte LDS-DMA loads, no register
 // staging), two LDS stages, one barrier per 64-wide K step.  A DMA instruction fills 1 KB of LDS
 // in lane order, i.e. 8 rows x 128 bytes; each lane picks the k piece that belongs in its slot,
@@ -940,6 +1023,14 @@ static hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
       }
     }
     return launch_plan<OT, EPI>(p, s, true);
+  } else {
+    // the line between the tiles: 1280-wide encoder layer, 2304 patches (at most 720 tiles of 128x128)
+    // 822 us with 128x128 tiles and 631 with 32x64; 15,552 patches (4880) 4886 and 5187
+    if ((long)((p.M + 127) / 128) * (p.N / 128) <= 1000) {
+      const unsigned wgs = (unsigned)((p.M + 31) / 32 * (p.N / 64));
+      hipLaunchKernelGGL((gemm_f32_small_kernel<EPI>), dim3(wgs), dim3(256), 0, s, p);
+      return hipGetLastError();
+    }
   }
   return launch_tile<TA, OT, EPI, 128, 128, 64, 64>(p, s);
 }

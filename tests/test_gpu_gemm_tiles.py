@@ -59,6 +59,20 @@ def test_vit_patch_embed_positions(gpu_lib):
             assert vlm.max_rel_err(out[i], vlm.vit_encode(imgs[i], wt, cfg)) < sc.TOL_BF16, f"image {i}"
 
 
+# fp32 mode on both sides of its tile rule: 15x60 patches (all projections as 32x64 tiles, ragged rows)
+# and 60x60 (the MLP up projection as 29 x 40 tiles of 128x128)
+@pytest.mark.parametrize("h,w", [(60, 240), (240, 240)])
+def test_vit_f32_tiles(gpu_lib, h, w):
+    import torch
+    cfg = synth.VitConfig(hidden=1280, heads=16, mlp=5120, layers=1, patch=4, merge=1, out_hidden=256, image_h=h,
+                          image_w=w, name=f"vit_f32_{h}x{w}")
+    wt = synth.vit_weights(cfg, seed=8)
+    img = synth.image(1, h, w, seed=3)
+    out = gpu_lib.Vit(cfg, wt, act=gpu_lib.ACT_F32).encode(torch.from_numpy(img).cuda().to(torch.bfloat16))[0].cpu().numpy()
+    tokens = [0, 59, 60, 450, cfg.n_patches - 1]
+    assert vlm.max_rel_err(out[tokens], vlm.vit_encode_tokens(img[0], wt, cfg, tokens)) < sc.TOL_F32
+
+
 @pytest.mark.parametrize("n_vis,n_text", [(0, 1), (3, 30), (0, 33), (70, 60)])
 def test_prefill_few_rows(gpu_lib, n_vis, n_text):
     import torch
