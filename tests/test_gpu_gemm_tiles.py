@@ -59,6 +59,22 @@ def test_vit_patch_embed_positions(gpu_lib):
             assert vlm.max_rel_err(out[i], vlm.vit_encode(imgs[i], wt, cfg)) < sc.TOL_BF16, f"image {i}"
 
 
+# patch extraction: odd patch sizes and row lengths (scalar and 16-byte image loads), more than 16 patches
+# per grid row with a ragged last group, one patch, and patches too large for the LDS tile
+@pytest.mark.parametrize("patch,h,w", [(7, 21, 133), (14, 28, 14 * 37), (16, 32, 16 * 21), (40, 40, 120), (75, 75, 150),
+                                       (14, 14, 14)])
+def test_patch_extraction(gpu_lib, patch, h, w):
+    import torch
+    cfg = synth.VitConfig(hidden=128, heads=2, mlp=128, layers=0, patch=patch, merge=1, out_hidden=128, image_h=h,
+                          image_w=w, name=f"vit_patch{patch}_{h}x{w}")
+    wt = synth.vit_weights(cfg, seed=8)
+    imgs = synth.image(3, h, w, seed=3)
+    for act, tol in ((gpu_lib.ACT_BF16, sc.TOL_BF16), (gpu_lib.ACT_F32, sc.TOL_F32)):
+        out = gpu_lib.Vit(cfg, wt, act=act).encode(torch.from_numpy(imgs).cuda().to(torch.bfloat16)).float().cpu().numpy()
+        for i in range(3):
+            assert vlm.max_rel_err(out[i], vlm.vit_encode(imgs[i], wt, cfg)) < tol, f"image {i}"
+
+
 # fp32 mode on both sides of its tile rule: 15x60 patches (all projections as 32x64 tiles, ragged rows)
 # and 60x60 (the MLP up projection as 29 x 40 tiles of 128x128)
 @pytest.mark.parametrize("h,w", [(60, 240), (240, 240)])
