@@ -844,10 +844,19 @@ static int causal_key_ranges(AttnArgs& q, int qblock, int threads) {
   if (q.part == nullptr || q.counters == nullptr || q.batch <= 0 || q.n_q <= 0) return 0;
   const int nqb = (q.sq + qblock - 1) / qblock, pairs = q.batch * q.n_q;
   const long slots_gpu = 2L * (q.cus > 0 ? q.cus : 256);
-  if ((long)nqb * pairs > slots_gpu) return 0;
+  if (!q.last_block && (long)nqb * pairs > slots_gpu) return 0;
   auto tiles = [&](int qb) { return (std::min(q.sk, (qb + 1) * qblock) + AK - 1) / AK; };
   const int most = tiles(nqb - 1);
   constexpr size_t PV = (D + 31) / 32 * 16 + 2;        // fp32 values per thread and range
+  if (q.last_block) {      // one block per pair: as many ranges as the merge takes, of 4 tiles or more
+    for (int tmax = std::max(4, (most + 7) / 8); tmax < most; ++tmax) {
+      const int P = (most + tmax - 1) / tmax;
+      if ((long)P * pairs > slots_gpu || (size_t)pairs * P * PV * threads * sizeof(float) > q.part_bytes) continue;
+      q.kv_tmax = tmax, q.kv_units = P, q.kv_slots = P;
+      return P;
+    }
+    return 0;
+  }
   for (int tmax = 4; tmax < most; ++tmax) {
     if ((most + tmax - 1) / tmax > 8) continue;
     int units = 0, slots = 0;
@@ -885,7 +894,8 @@ static hipError_t attn_launch(const AttnArgs& p, hipStream_t s) {
     constexpr int NW = 4;
     AttnArgs q = p;
     int units = causal_key_ranges<D>(q, NW * 32, NW * 64);
-    if (units == 0) units = (p.sq + NW * 32 - 1) / (NW * 32);
+    // (the grid runs from the last, heaviest block down)
+    if (units == 0) units = p.last_block ? 1 : (p.sq + NW * 32 - 1) / (NW * 32);
     hipLaunchKernelGGL((attn_kernel<T, D, true, NW>), dim3(units * p.n_q * p.batch), dim3(NW * 64), 0, s, q);
   } else {
     hipLaunchKernelGGL((attn_kernel<T, D, false, 4>), dim3((p.sq + AQ - 1) / AQ * p.n_q * p.batch), dim3(256), 0, s, p);

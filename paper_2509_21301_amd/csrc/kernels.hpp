@@ -108,6 +108,7 @@ struct AttnArgs {
   // partials land in part; the last range of a block to finish merges them
   unsigned* counters = nullptr;
   int kv_tmax = 0, kv_units = 0, kv_slots = 0;   // set by the launcher
+  bool last_block = false;    // causal: only the last block of 128 queries is computed (and written)
 };
 template <typename T>
 hipError_t attention(const AttnArgs& p, int head_dim, hipStream_t s);

@@ -722,11 +722,12 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
     GemmArgs p = g;
     int slices = 0;
     p.slices_out = &slices;
+    float* xr = (float*)p.out;
     CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_RESID, s)));
     if (slices > 0)
-      CALL(NOVA_KIND_MISC, s, nova::split_norm_rows<T>(split_ws, slices, (size_t)S * H, x, S, H, gain, nullptr, c.eps, 0, a, H, s));
+      CALL(NOVA_KIND_MISC, s, nova::split_norm_rows<T>(split_ws, slices, (size_t)p.M * H, xr, p.M, H, gain, nullptr, c.eps, 0, a, H, s));
     else
-      CALL(NOVA_KIND_MISC, s, nova::norm_rows<T>(x, S, H, gain, nullptr, c.eps, 0, a, H, 1, 0, 0, s));
+      CALL(NOVA_KIND_MISC, s, nova::norm_rows<T>(xr, p.M, H, gain, nullptr, c.eps, 0, a, H, 1, 0, 0, s));
     return (int)NOVA_OK;
   };
   for (int l = 0; l < c.layers; ++l) {
@@ -734,6 +735,13 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
     auto W = [&](int i) { return (const bf16_t*)(lw + m->lay.off[i]); };
     T* kp = (T*)kv->k + l * kv_layer;
     T* vp = (T*)kv->v + l * kv_layer;
+    // The last layer writes every position's K and V, but past its attention only the last row is read
+    // (the head takes row S - 1): its queries are the last block's, and its O and MLP projections and
+    // norm run on that row: 3% of a 28-layer prefill (1500 tokens 19.33 -> 18.68 ms, of which the GEMM tiles
+    // gave 0.2; 3579 tokens 44.4 -> 43.1 ms).
+    const bool tail = l + 1 == c.layers;
+    const int rows = tail ? 1 : S;                       // rows of the O and MLP projections, from row0 on
+    const size_t row0 = (size_t)(S - rows);
     if (l == 0)      // later layers: the previous layer's down projection normalised x already
       CALL(NOVA_KIND_MISC, s, nova::norm_rows<T>(x, S, H, W(0), nullptr, c.eps, 0, a, H, 1, 0, 0, s));
     {
@@ -747,20 +755,21 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
       // the split-K partials are free between the QKV and O projections: the attention's key
       // ranges keep theirs there
       p.part = split_ws, p.part_bytes = prefill_split_floats(m, S) * sizeof(float), p.counters = att_cnt, p.cus = cus;
+      p.last_block = tail;
       CALL(NOVA_KIND_ATTN, s, nova::attention<T>(p, D, s));
     }
-    if (int rc = resid_then_norm(with_split(GemmArgs{att, qd, W(2), qd, S, H, qd, nullptr, x, H, nullptr, 0}), W(3)))
+    if (int rc = resid_then_norm(with_split(GemmArgs{att + row0 * qd, qd, W(2), qd, rows, H, qd, nullptr, x + row0 * H, H, nullptr, 0}), W(3)))
       return rc;
     {
-      const GemmArgs p = with_split(GemmArgs{a, H, W(4), H, S, 2 * m->ip, H, nullptr, hm, m->ip, nullptr, 0});
+      const GemmArgs p = with_split(GemmArgs{a, H, W(4), H, rows, 2 * m->ip, H, nullptr, hm, m->ip, nullptr, 0});
       CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_SWIGLU, s)));
     }
     {
-      const GemmArgs p = with_split(GemmArgs{hm, m->ip, W(5), m->ip, S, H, m->ip, nullptr, x, H, nullptr, 0});
-      if (l + 1 < c.layers) {   // with the next layer's input norm
+      const GemmArgs p = with_split(GemmArgs{hm, m->ip, W(5), m->ip, rows, H, m->ip, nullptr, x + row0 * H, H, nullptr, 0});
+      if (!tail) {   // with the next layer's input norm
         const bf16_t* next_gain = (const bf16_t*)((const char*)m->d.layers + (size_t)(l + 1) * m->lay.bytes + m->lay.off[0]);
         if (int rc = resid_then_norm(p, next_gain)) return rc;
-      } else {                  // the last layer: the final norm reads the last row only
+      } else {                  // the final norm follows
         CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_RESID, s)));
       }
     }
