@@ -32,6 +32,7 @@ constexpr int GV_KC = 256;             // K chunk per pipeline step (32 pieces o
 constexpr int GV_RW = 16;              // weight rows per wave
 constexpr int GV_ROWS = 4 * GV_RW;     // rows per workgroup (4 waves)
 constexpr int GV_MAX_SPLITS = 16;
+constexpr int GV_TAIL_MAX = 4;         // K slices of a tail tile at most
 
 // K splits: as many as keep the workgroups (64 rows each) within the stream's compute units, one
 // workgroup per CU.  Measured on the decode shapes at 64, 128 and 256 CUs, a CU streams one
@@ -58,6 +59,81 @@ size_t gemv_partial_floats(int B, int N, int K, bool f32x, int cus) {
 // slot (k/8) ^ (row % 16).
 __device__ __forceinline__ int swz(int row, int piece) { return row * GV_KC + 8 * (piece ^ (row & 15)); }
 
+// The K slices of the gate/up projection's last row tiles.  With one workgroup per 64 rows, N / 64 = 592
+// tiles on 256 CUs are 2.3 rounds: 80 CUs stream three tiles while the others stream two.  The 80 tiles past
+// the last whole round are cut into the number of K slices (at most 4, as many as the workspace and the
+// arrival counters hold) that gives the busiest CU the least to stream: 3 slices, a third of a tile each.
+// Decode steps with and without (and with gate/up on the ring below 17 rows): batch 1, 4 layers 636 -> 624 us,
+// batch 8, 8 layers 1148 -> 1120, batch 32 at context 3627 872 -> 857, batch 8 on 128 CUs 850 -> 845.
+// 1: no slices.
+static int gemv_tail(const GemvArgs& p) {
+  const int tiles = p.N / GV_ROWS, tail = tiles % p.cus, chunks = p.K / GV_KC;
+  if (tiles < p.cus || tail == 0 || p.counters == nullptr || tail > p.n_counters || p.partial == nullptr) return 1;
+  int best = 1;
+  auto share = [&](int s) { return (double)((tail * s + p.cus - 1) / p.cus) * ((chunks + s - 1) / s) / chunks; };
+  for (int s = 2; s <= GV_TAIL_MAX; ++s) {
+    if ((s - 1) * ((chunks + s - 1) / s) >= chunks) continue;           // an empty slice
+    if ((size_t)s * tail * GV_ROWS * p.B > p.partial_floats) break;
+    if (share(s) < share(best)) best = s;
+  }
+  return best;
+}
+
+// One K slice's fp32 products of a tail tile (scaled by the row's norm already: the scale is a factor of
+// every slice) written through to the device-coherent level; the tile's last slice to arrive sums them in
+// slice order and applies the SwiGLU.  Ordering as in the residual fold below: every thread waits until its
+// stores are acknowledged before the workgroup counts its arrival.
+template <typename OT, int NB>
+__device__ __forceinline__ void gemv_tail_finish(const GemvArgs& p, const f32x4 (&acc)[NB], int tail_tile, int n_tail,
+                                                 int split, int nsplit, int row0) {
+  __shared__ int last;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  float* part = p.partial + (size_t)tail_tile * p.B * GV_ROWS;          // [slice][tail tile][B][64 rows]
+  const size_t stride = (size_t)n_tail * p.B * GV_ROWS;
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int b = j * 16 + (lane & 15);
+    if (b >= p.B) continue;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      __hip_atomic_store(part + split * stride + (size_t)b * GV_ROWS + wave * GV_RW + (lane >> 4) * 4 + r, acc[j][r],
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (tid == 0)
+    last = __hip_atomic_fetch_add(p.counters + tail_tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           (unsigned)(nsplit - 1);
+  __syncthreads();
+  if (!last) return;
+  // thread: output column tid % 32 of batch rows tid / 32 + 8 i; all loads before any sum
+  constexpr int IT = 2 * NB;
+  const int c = tid & 31, n = (c >> 3) * 16 + (c & 7);                  // gate row; its up row is 8 further
+  float g[GV_TAIL_MAX][IT], u[GV_TAIL_MAX][IT];
+#pragma unroll
+  for (int s = 0; s < GV_TAIL_MAX; ++s)
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const float* src = part + min(s, nsplit - 1) * stride + (size_t)min((tid >> 5) + 8 * i, p.B - 1) * GV_ROWS + n;
+      g[s][i] = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      u[s][i] = __hip_atomic_load(src + 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    const int b = (tid >> 5) + 8 * i;
+    float gate = 0.f, up = 0.f;
+#pragma unroll
+    for (int s = 0; s < GV_TAIL_MAX; ++s)
+      if (s < nsplit) {
+        gate += g[s][i];
+        up += u[s][i];
+      }
+    if (b < p.B)
+      reinterpret_cast<OT*>(p.out)[(size_t)b * p.ldo + ((row0 + tail_tile * GV_ROWS) >> 1) + c] = from_f<OT>(silu(gate) * up);
+  }
+  if (tid == 0) __hip_atomic_store(p.counters + tail_tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // TA: activation type of X (bf16, or fp32 for the exact mode whose operands are split into bf16
 // hi + lo).  NSCALE: X holds x * gain of a folded RMSNorm; output columns are scaled by the row's
 // rsqrt(mean x^2 + eps), from the producer's per-tile sums of squares.
@@ -72,9 +148,13 @@ __device__ __forceinline__ int swz(int row, int piece) { return row * GV_KC + 8 
 // 195 -> 190 us, at batch 1 182 -> 181 us.
 constexpr int GV_BK = 64;              // ring: K per stage
 
-template <typename TA, typename OT, int NB, int EPI, bool DIRECT, bool NSCALE, bool RING, int ROWS>
+// TAIL (SwiGLU): the row tiles past the last whole round of one workgroup per CU, p.N / 64 % cus of them,
+// are cut into kc-long K slices that run in the same launch, behind the whole tiles; a tile's last slice to
+// arrive sums them in slice order (gemv_tail holds the rule).
+template <typename TA, typename OT, int NB, int EPI, bool DIRECT, bool NSCALE, bool RING, int ROWS, bool TAIL = false>
 __global__ void __launch_bounds__(ROWS * 4) gemv_kernel(GemvArgs p, int kc) {
   static_assert(ROWS == GV_ROWS || (RING && EPI != EPI_RESID), "wide workgroups: ring, no residual epilogue");
+  static_assert(!TAIL || (EPI == EPI_SWIGLU && DIRECT && ROWS == GV_ROWS), "tail slices: SwiGLU in 64-row tiles");
   constexpr int NWV = ROWS / GV_RW;                       // waves
   constexpr int GV_NST = ROWS == GV_ROWS ? 5 : 3;         // ring stages: 60 KB, two workgroups per CU
   using TX = TA;
@@ -92,9 +172,13 @@ __global__ void __launch_bounds__(ROWS * 4) gemv_kernel(GemvArgs p, int kc) {
   __shared__ unsigned long long am_s[EPI == EPI_ARGMAX ? NWV : 1][16];   // per-wave argmax keys
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n_base = blockIdx.x * ROWS + wave * GV_RW;
-  const int split = blockIdx.y;
-  const int k_begin = split * kc, k_end = min(k_begin + kc, p.K);
+  const int tiles = TAIL ? p.N / ROWS : 0, n_tail = TAIL ? tiles % p.cus : 0, whole = tiles - n_tail;
+  const bool slice = TAIL && (int)blockIdx.x >= whole;    // a K slice of a tail tile
+  const int tail_tile = slice ? ((int)blockIdx.x - whole) % n_tail : 0;
+  const int tile = slice ? whole + tail_tile : blockIdx.x;
+  const int n_base = tile * ROWS + wave * GV_RW;
+  const int split = TAIL ? (slice ? ((int)blockIdx.x - whole) / n_tail : 0) : blockIdx.y;
+  const int k_begin = split * kc, k_end = TAIL && !slice ? p.K : min(k_begin + kc, p.K);
   const int n = lane & 15, g = lane >> 4;          // MFMA operand row and k group
   const int h = lane >> 5, pc = lane & 31;         // load row within a pair, piece
 
@@ -133,7 +217,7 @@ __global__ void __launch_bounds__(ROWS * 4) gemv_kernel(GemvArgs p, int kc) {
     for (int t = 0; t < IT; ++t) {
       const int r = min(wave + NWV * t, NQ - 1) * 8 + (lane >> 3), k = k_begin + 8 * ((lane & 7) ^ ((r >> 1) & 7));
       src[t] = r < XROWS ? reinterpret_cast<const bf16_t*>(p.X) + (size_t)min(r, p.B - 1) * p.ldx + k
-                         : p.W + (size_t)(blockIdx.x * ROWS + r - XROWS) * p.ldw + k;
+                         : p.W + (size_t)(tile * ROWS + r - XROWS) * p.ldw + k;
     }
     const uint32_t lbase = lds_addr_of(xs) + (uint32_t)(wave * 8 * GV_BK) * 2u;
     auto dma = [&](int kt, int stage) {
@@ -285,6 +369,12 @@ __global__ void __launch_bounds__(ROWS * 4) gemv_kernel(GemvArgs p, int kc) {
       const float rstd = rstd_s[min(j * 16 + (lane & 15), p.B - 1)];
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[j][r] *= rstd;
+    }
+  }
+  if constexpr (TAIL) {
+    if (slice) {
+      gemv_tail_finish<OT, NB>(p, acc, tail_tile, n_tail, split, ((int)gridDim.x - whole) / n_tail, whole * ROWS);
+      return;
     }
   }
 #pragma unroll
@@ -479,7 +569,11 @@ __global__ void gemv_reduce(GemvArgs p, int splits) {
 
 template <typename TA, typename OT, int NB, int EPI, bool NSCALE>
 static hipError_t gemv_launch(const GemvArgs& p, hipStream_t s) {
-  constexpr bool F32X = sizeof(TA) == 4, RING = NB == 2 && !F32X;
+  // gate/up takes the ring at every batch size: its 35 registers let three workgroups share a CU where the
+  // register path's 176 let two (4-layer decode steps, 8 sequences: 1118 against 1128 us for 8 layers, batch
+  // 1 623 against 625).  The split projections of up to 16 rows stay on the register path, which streams
+  // faster where a CU holds one workgroup (batch 8 on 128 CUs: 845 us against 888 with the ring).
+  constexpr bool F32X = sizeof(TA) == 4, RING = !F32X && (NB == 2 || EPI == EPI_SWIGLU);
   const int splits = gemv_splits(p.N, p.K, p.B, F32X, p.cus);
   const int chunks = p.K / GV_KC;
   const int kc = (chunks + splits - 1) / splits * GV_KC;
@@ -488,6 +582,15 @@ static hipError_t gemv_launch(const GemvArgs& p, hipStream_t s) {
     // 128-row workgroups while they make at least two rounds of two per CU
     if (splits == 1 && p.N % 128 == 0 && p.N / 128 >= 4 * p.cus) {
       hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, true, NSCALE, true, 128>), dim3(p.N / 128), dim3(512), 0, s, p, kc);
+      return hipGetLastError();
+    }
+  }
+  if constexpr (EPI == EPI_SWIGLU) {
+    const int slices = splits == 1 ? gemv_tail(p) : 1;
+    if (slices > 1) {
+      const int tiles = p.N / GV_ROWS, tail = tiles % p.cus;
+      hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, true, NSCALE, RING, GV_ROWS, true>), dim3(tiles + tail * (slices - 1)),
+                         dim3(256), 0, s, p, (chunks + slices - 1) / slices * GV_KC);
       return hipGetLastError();
     }
   }
@@ -513,8 +616,8 @@ hipError_t gemv(const GemvArgs& p, int epi, hipStream_t s) {
   if (p.B > 32 || p.N % GV_ROWS || p.K <= 0 || p.K % GV_KC || p.ldx % 8 || p.ldw % 8 || p.cus <= 0) return hipErrorInvalidValue;
   if (epi == EPI_ARGMAX && (!p.argmax_keys || p.N % 64)) return hipErrorInvalidValue;
   if (p.ss_in != nullptr && (p.ss_parts <= 0 || p.ss_parts > 64)) return hipErrorInvalidValue;
-  if ((p.ss_out != nullptr || p.counters != nullptr || p.gain_out != nullptr) && (epi != EPI_RESID || p.out == nullptr))
-    return hipErrorInvalidValue;
+  if ((p.ss_out != nullptr || p.gain_out != nullptr) && (epi != EPI_RESID || p.out == nullptr)) return hipErrorInvalidValue;
+  if (p.counters != nullptr && ((epi != EPI_RESID && epi != EPI_SWIGLU) || p.out == nullptr)) return hipErrorInvalidValue;
   if (p.gain_out != nullptr && p.aout == nullptr) return hipErrorInvalidValue;
   const bool two = p.B > 16, norm = p.ss_in != nullptr;
 #define NOVA_GEMV_CASE(E)                                                                                 \

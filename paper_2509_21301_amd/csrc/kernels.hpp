@@ -76,6 +76,10 @@ struct GemvArgs {
   const bf16_t* gain_out = nullptr;
   void* aout = nullptr;
   int ldao = 0;
+  // EPI_SWIGLU: with n_counters arrival counters (zero on entry, zero again on exit) and partial_floats
+  // floats at partial, the row tiles past the last whole round of the CUs may be cut into K slices.
+  int n_counters = 0;
+  size_t partial_floats = 0;
   // compute units the launch's stream may use (its CU partition, or the whole GPU): the K split
   // is chosen from it
   int cus = 0;

@@ -639,10 +639,11 @@ struct DecodeBufs {
   T* hm;                      // MLP hidden
   unsigned long long* keys;   // greedy argmax keys
   float* ss;                  // per-tile row sums of squares of the 2 L + 1 fused RMSNorms [2L+1][H/64][B]
-  unsigned* counters;         // split-K arrival counters of the O and down projections [2L][H/64]
+  unsigned* counters;         // arrival counters of the O and down (and gate/up) projections [2L][H/64]
   float* rope;                // rotary sines and cosines of each sequence's position [B][2][D/2]
   float* part;                // split-K partials
   float* apart;               // decode-attention split partials
+  size_t mlp_floats;          // floats from part to the end: all free between the O and down projections
   size_t used;
 };
 
@@ -673,6 +674,7 @@ DecodeBufs<T> decode_bufs(const nova_llm* m, int B, int max_ctx, void* base) {
   d.part = w.take<float>(part);
   d.apart = w.take<float>(nova::dec_attn_partial_floats(B, c.n_q, c.head_dim, max_ctx, c.n_kv));
   d.used = w.used;
+  d.mlp_floats = ((char*)base + w.used - (char*)d.part) / sizeof(float);
   return d;
 }
 }  // namespace
@@ -842,6 +844,8 @@ int llm_decode_t(const nova_llm* m, const int* ids, const int* pos, const int* t
         GemvArgs p{d.a, H, W(4), H, B, 2 * m->ip, H, d.hm, m->ip, d.part, nullptr};
         p.cus = cus;
         p.ss_in = ss(2 * l + 1), p.ss_parts = tiles, p.eps = c.eps;
+        // the arrival counters of this layer's O and down projections, which are all zero in between
+        p.counters = d.counters + (size_t)(2 * l) * tiles, p.n_counters = 2 * tiles, p.partial_floats = d.mlp_floats;
         CALL(NOVA_KIND_GEMV, s, (nova::gemv<T, T>(p, nova::EPI_SWIGLU, s)));
       }
       {
@@ -865,7 +869,7 @@ int llm_decode_t(const nova_llm* m, const int* ids, const int* pos, const int* t
     auto ss = [&](int k) { return d.ss + (size_t)k * tiles * B; };
     CALL(NOVA_KIND_MISC, s, nova::decode_embed<T>(ids, B, (const bf16_t*)m->d.embed, H,
                                                   c.layers > 0 ? layer_w(0, 0) : final_gain, d.x, d.a, ss(0), tiles, d.keys,
-                                                  nullptr, 0, pos, c.rope_theta, D, d.rope, s));
+                                                  d.counters, 2 * c.layers * tiles, pos, c.rope_theta, D, d.rope, s));
     for (int l = 0; l < c.layers; ++l) {
       auto W = [&](int i) { return layer_w(l, i); };
       {
@@ -886,6 +890,8 @@ int llm_decode_t(const nova_llm* m, const int* ids, const int* pos, const int* t
         GemvArgs p{d.a, H, W(4), H, B, 2 * m->ip, H, d.hm, m->ip, d.part, nullptr};
         p.cus = cus;
         p.ss_in = ss(2 * l + 1), p.ss_parts = tiles, p.eps = c.eps;
+        // the arrival counters of this layer's O and down projections, which are all zero in between
+        p.counters = d.counters + (size_t)(2 * l) * tiles, p.n_counters = 2 * tiles, p.partial_floats = d.mlp_floats;
         CALL(NOVA_KIND_GEMV, s, (nova::gemv<T, T>(p, nova::EPI_SWIGLU, s)));
       }
       {

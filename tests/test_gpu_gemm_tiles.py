@@ -148,3 +148,39 @@ def test_decode_wide_head(gpu_lib, bsz):
     for b in range(bsz):
         assert vlm.max_rel_err(got[b], ref[b]) < sc.TOL_BF16, f"seq {b}"
     assert np.array_equal(nxt.cpu().numpy(), np.argmax(got, axis=1))      # the fused argmax, lowest id on ties
+
+
+# gate/up of 8 x units row tiles: 8 or 32 tiles past the GPU's 256 compute units (one and two column groups,
+# 4 chunks of K over 2..4 slices), 40 (more than the arrival counters hold: no slices), 200 on a partition of
+# 64 compute units, and 264 tiles in fp32; a second step on the same workspace finds its counters zero again
+@pytest.mark.parametrize("bsz,units,cus,act", [(1, 33, 0, "bf16"), (8, 36, 0, "bf16"), (17, 36, 0, "bf16"),
+                                               (32, 33, 0, "bf16"), (5, 37, 0, "bf16"), (3, 25, 64, "bf16"),
+                                               (16, 33, 0, "f32")])
+def test_decode_gate_up_tail(gpu_lib, bsz, units, cus, act):
+    import torch
+    cfg = synth.LlmConfig(hidden=1024, n_q=16, n_kv=4, head_dim=64, inter=256 * units, vocab=4096, layers=2, name="llm_tail")
+    wt = synth.llm_weights(cfg, seed=2)
+    ctx = [5 + 3 * b for b in range(bsz)]
+    tables, pool = synth.block_tables([c + 1 for c in ctx], cfg.block, seed=9)
+    rng = np.random.default_rng(3)
+    kref = vlm.PagedKV(cfg.layers, pool, cfg.n_kv, cfg.block, cfg.head_dim)
+    kref.k[:] = synth.bf16_round(rng.standard_normal(kref.k.shape, dtype=np.float32))
+    kref.v[:] = synth.bf16_round(rng.standard_normal(kref.v.shape, dtype=np.float32))
+    llm = gpu_lib.Llm(cfg, wt, act=gpu_lib.ACT_F32 if act == "f32" else gpu_lib.ACT_BF16)
+    kv = gpu_lib.KvPool(llm, pool)
+    kv.k5.copy_(torch.from_numpy(kref.k.astype(np.float32)).to(kv.k5.dtype))
+    kv.v5.copy_(torch.from_numpy(np.swapaxes(kref.v, -1, -2).astype(np.float32)).to(kv.v5.dtype))
+    ids, pos = synth.text_ids(bsz, cfg.vocab, seed=12), np.array(ctx, np.int32)
+    stream = gpu_lib.set_stage_partition(gpu_lib.STAGE_DECODE, gpu_lib.make_cu_mask(cus)) if cus else None
+    args = [torch.from_numpy(a).cuda() for a in (ids, pos, tables)]
+    steps = []
+    for _ in range(2):
+        logits = torch.full((bsz, cfg.vocab), float("nan"), dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        llm.decode(*args, kv, max_ctx=max(ctx) + 1, logits=logits, stream=stream)
+        torch.cuda.synchronize()
+        steps.append(logits.cpu().numpy())
+    ref, _ = vlm.llm_decode_step(ids, pos, tables, kref, wt, cfg)
+    for b in range(bsz):
+        assert vlm.max_rel_err(steps[0][b], ref[b]) < (sc.TOL_F32 if act == "f32" else sc.TOL_BF16), f"seq {b}"
+    assert np.array_equal(steps[0], steps[1])
