@@ -464,23 +464,76 @@ hipError_t argmax_finish(const unsigned long long* keys, int B, int* ids, hipStr
 }
 
 // ------------------------------------------------------------------ embedding gather
-template <typename T>
-__global__ void embed_kernel(const T* __restrict__ vis, int n_vis, const int* __restrict__ ids, int n_ids,
-                             const bf16_t* __restrict__ embed, int H, float* __restrict__ x) {
-  const long total = (long)(n_vis + n_ids) * H;
-  for (long idx = (long)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (long)gridDim.x * blockDim.x) {
-    const int r = (int)(idx / H), c = (int)(idx % H);
-    x[idx] = r < n_vis ? to_f<T>(vis[(size_t)r * H + c]) : bf2f(embed[(size_t)ids[r - n_vis] * H + c]);
+// The prompt's rows (vision rows, then the ids' embedding rows) into the fp32 residual stream x, and with a
+// gain their RMSNorm into a: one wave per row, held in registers as in the norm kernel, with its order of
+// sums.  Bound by HBM.  One element per thread with two 64-bit divisions, and x read again by a norm pass,
+// took 17.6 + 8.2 us for 1500 x 3584 rows; 10.8 us now.
+template <typename T, int NV>
+__global__ void __launch_bounds__(256) embed_kernel(const T* __restrict__ vis, int n_vis, const int* __restrict__ ids,
+                                                    int n_rows, const bf16_t* __restrict__ embed, int H,
+                                                    const bf16_t* __restrict__ g, float eps, float* __restrict__ x,
+                                                    T* __restrict__ a) {
+  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6), n4 = H / 4;
+  if (row >= n_rows) return;
+  uint2 gg[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = j * 64 + lane;
+    gg[j] = g != nullptr && i < n4 ? *reinterpret_cast<const uint2*>(g + 4 * i) : make_uint2(0u, 0u);
+  }
+  auto unpack = [](uint2 r) {
+    return float4{bf2f((bf16_t)(r.x & 0xffff)), bf2f((bf16_t)(r.x >> 16)), bf2f((bf16_t)(r.y & 0xffff)),
+                  bf2f((bf16_t)(r.y >> 16))};
+  };
+  float4 v[NV];
+  if (row >= n_vis || sizeof(T) == 2) {
+    const bf16_t* src = row < n_vis ? reinterpret_cast<const bf16_t*>(vis) + (size_t)row * H
+                                    : embed + (size_t)ids[row - n_vis] * H;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int i = j * 64 + lane;
+      v[j] = unpack(i < n4 ? *reinterpret_cast<const uint2*>(src + 4 * i) : make_uint2(0u, 0u));
+    }
+  } else {
+    const float* src = reinterpret_cast<const float*>(vis) + (size_t)row * H;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int i = j * 64 + lane;
+      v[j] = i < n4 ? *reinterpret_cast<const float4*>(src + 4 * i) : float4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = j * 64 + lane;
+    if (i < n4) {
+      *reinterpret_cast<float4*>(x + (size_t)row * H + 4 * i) = v[j];
+      ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
+    }
+  }
+  if (g == nullptr) return;
+  const float rstd = rsqrtf(wave_sum(ss) / H + eps);
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = j * 64 + lane;
+    if (i >= n4) continue;
+    const float4 w = unpack(gg[j]);
+    const float y[4] = {v[j].x * rstd * w.x, v[j].y * rstd * w.y, v[j].z * rstd * w.z, v[j].w * rstd * w.w};
+    T* o = a + (size_t)row * H + 4 * i;
+    if constexpr (sizeof(T) == 4) *reinterpret_cast<float4*>(o) = float4{y[0], y[1], y[2], y[3]};
+    else *reinterpret_cast<uint2*>(o) = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
   }
 }
 
 template <typename T>
-hipError_t embed_rows(const T* vis, int n_vis, const int* ids, int n_ids, const bf16_t* embed, int H, float* x,
-                      hipStream_t s) {
-  const long total = (long)(n_vis + n_ids) * H;
-  if (total <= 0) return hipSuccess;
-  const int grid = (int)std::min<long>((total + 255) / 256, 65536);
-  hipLaunchKernelGGL((embed_kernel<T>), dim3(grid), dim3(256), 0, s, vis, n_vis, ids, n_ids, embed, H, x);
+hipError_t embed_rows(const T* vis, int n_vis, const int* ids, int n_ids, const bf16_t* embed, int H, const bf16_t* g,
+                      float eps, float* x, T* a, hipStream_t s) {
+  const int rows = n_vis + n_ids;
+  if (rows <= 0) return hipSuccess;
+  if (H % 4 || H > 4096) return hipErrorInvalidValue;
+  const dim3 grid((rows + 3) / 4);
+  if (H <= 1024) hipLaunchKernelGGL((embed_kernel<T, 4>), grid, dim3(256), 0, s, vis, n_vis, ids, rows, embed, H, g, eps, x, a);
+  else hipLaunchKernelGGL((embed_kernel<T, 16>), grid, dim3(256), 0, s, vis, n_vis, ids, rows, embed, H, g, eps, x, a);
   return hipGetLastError();
 }
 
@@ -498,18 +551,18 @@ __global__ void __launch_bounds__(256) decode_embed_kernel(const int* __restrict
                                                            float* __restrict__ rope) {
   __shared__ float red[4];
   const int b = blockIdx.x, B = gridDim.x;
+  // Bound by latency (one workgroup per sequence): 4 elements per thread and iteration, every load issued before
+  // the rest of the work (H <= 4096).  2-byte loads in a loop of 14 round trips took 9.0 us at H 3584, 4.7 now.
+  constexpr int NV = 4;
+  const int n4 = H / 4;
   const bf16_t* e = embed + (size_t)ids[b] * H;
-  float* xr = x + (size_t)b * H;
-  T* ar = a + (size_t)b * H;
-  float ss = 0.f;
-  for (int c = threadIdx.x; c < H; c += 256) {
-    const float v = bf2f(e[c]);
-    xr[c] = v;
-    ar[c] = from_f<T>(v * bf2f(g[c]));
-    ss += v * v;
+  uint2 ev[NV], gv[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = min(j * 256 + (int)threadIdx.x, n4 - 1);
+    ev[j] = *reinterpret_cast<const uint2*>(e + 4 * i);
+    gv[j] = *reinterpret_cast<const uint2*>(g + 4 * i);
   }
-  ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   for (int t = 1 + threadIdx.x; t < ss_parts; t += 256) ss0[(size_t)t * B + b] = 0.f;
   if (threadIdx.x == 0) keys[b] = 0ull;
   if (b == 0)
@@ -521,6 +574,23 @@ __global__ void __launch_bounds__(256) decode_embed_kernel(const int* __restrict
     rope[(size_t)b * D + c] = sn;
     rope[(size_t)b * D + D / 2 + c] = cs;
   }
+  float ss = 0.f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = j * 256 + threadIdx.x;
+    if (i >= n4) break;
+    const float v[4] = {bf2f((bf16_t)(ev[j].x & 0xffff)), bf2f((bf16_t)(ev[j].x >> 16)),
+                        bf2f((bf16_t)(ev[j].y & 0xffff)), bf2f((bf16_t)(ev[j].y >> 16))};
+    const float y[4] = {v[0] * bf2f((bf16_t)(gv[j].x & 0xffff)), v[1] * bf2f((bf16_t)(gv[j].x >> 16)),
+                        v[2] * bf2f((bf16_t)(gv[j].y & 0xffff)), v[3] * bf2f((bf16_t)(gv[j].y >> 16))};
+    *reinterpret_cast<float4*>(x + (size_t)b * H + 4 * i) = float4{v[0], v[1], v[2], v[3]};
+    T* o = a + (size_t)b * H + 4 * i;
+    if constexpr (sizeof(T) == 4) *reinterpret_cast<float4*>(o) = float4{y[0], y[1], y[2], y[3]};
+    else *reinterpret_cast<uint2*>(o) = make_uint2(pack2(y[0], y[1]), pack2(y[2], y[3]));
+    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+  }
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
   if (threadIdx.x == 0) ss0[b] = red[0] + red[1] + red[2] + red[3];
 }
@@ -530,6 +600,7 @@ hipError_t decode_embed(const int* ids, int B, const bf16_t* embed, int H, const
                         int ss_parts, unsigned long long* keys, unsigned* counters, int n_counters, const int* pos,
                         float theta, int D, float* rope, hipStream_t s) {
   if (B <= 0) return hipSuccess;
+  if (H % 4 || H > 4096) return hipErrorInvalidValue;
   hipLaunchKernelGGL((decode_embed_kernel<T>), dim3(B), dim3(256), 0, s, ids, embed, H, g, x, a, ss0, ss_parts, keys,
                      counters, n_counters, pos, theta, D, rope);
   return hipGetLastError();
@@ -626,7 +697,9 @@ template hipError_t resid_rmsnorm<float>(const float*, int, float*, int, int, co
 template hipError_t resid_fold<bf16_t>(const float*, int, float*, int, int, const bf16_t*, bf16_t*, int, float*,
                                        hipStream_t);
 template hipError_t resid_fold<float>(const float*, int, float*, int, int, const bf16_t*, float*, int, float*, hipStream_t);
-template hipError_t embed_rows<bf16_t>(const bf16_t*, int, const int*, int, const bf16_t*, int, float*, hipStream_t);
-template hipError_t embed_rows<float>(const float*, int, const int*, int, const bf16_t*, int, float*, hipStream_t);
+template hipError_t embed_rows<bf16_t>(const bf16_t*, int, const int*, int, const bf16_t*, int, const bf16_t*, float, float*,
+                                       bf16_t*, hipStream_t);
+template hipError_t embed_rows<float>(const float*, int, const int*, int, const bf16_t*, int, const bf16_t*, float, float*, float*,
+                                      hipStream_t);
 
 }  // namespace nova

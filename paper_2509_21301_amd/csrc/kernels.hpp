@@ -190,8 +190,8 @@ hipError_t decode_embed(const int* ids, int B, const bf16_t* embed, int H, const
                         int ss_parts, unsigned long long* keys, unsigned* counters, int n_counters, const int* pos,
                         float theta, int D, float* rope, hipStream_t s);
 template <typename T>
-hipError_t embed_rows(const T* vis, int n_vis, const int* ids, int n_ids, const bf16_t* embed, int H, float* x,
-                      hipStream_t s);
+hipError_t embed_rows(const T* vis, int n_vis, const int* ids, int n_ids, const bf16_t* embed, int H, const bf16_t* g,
+                      float eps, float* x, T* a, hipStream_t s);   // g: the RMSNorm of the rows into a (null: none)
 hipError_t argmax_rows(const float* logits, int B, int V, int* out, hipStream_t s);
 hipError_t cu_probe(hipStream_t s, uint32_t* out, int n);
 

@@ -717,7 +717,9 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
     return p;
   };
 
-  CALL(NOVA_KIND_MISC, s, nova::embed_rows<T>(vis, n_vis, ids, n_text, (const bf16_t*)m->d.embed, H, x, s));
+  // the embedded rows, with the first layer's input norm
+  const bf16_t* gain0 = c.layers > 0 ? (const bf16_t*)((const char*)m->d.layers + m->lay.off[0]) : nullptr;
+  CALL(NOVA_KIND_MISC, s, nova::embed_rows<T>(vis, n_vis, ids, n_text, (const bf16_t*)m->d.embed, H, gain0, c.eps, x, a, s));
   // a residual projection (O, down) whose K is split leaves its slices for the RMSNorm that reads
   // x next to fold in (one pass over x instead of a reduction pass and a norm pass)
   auto resid_then_norm = [&](const GemmArgs& g, const bf16_t* gain) -> int {
@@ -744,8 +746,6 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
     const bool tail = l + 1 == c.layers;
     const int rows = tail ? 1 : S;                       // rows of the O and MLP projections, from row0 on
     const size_t row0 = (size_t)(S - rows);
-    if (l == 0)      // later layers: the previous layer's down projection normalised x already
-      CALL(NOVA_KIND_MISC, s, nova::norm_rows<T>(x, S, H, W(0), nullptr, c.eps, 0, a, H, 1, 0, 0, s));
     {
       const GemmArgs p = with_split(GemmArgs{a, H, W(1), H, S, m->qkvw, H, nullptr, qkv, m->qkvw, nullptr, 0});
       CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_STORE, s)));

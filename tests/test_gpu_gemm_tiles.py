@@ -184,3 +184,27 @@ def test_decode_gate_up_tail(gpu_lib, bsz, units, cus, act):
     for b in range(bsz):
         assert vlm.max_rel_err(steps[0][b], ref[b]) < (sc.TOL_F32 if act == "f32" else sc.TOL_BF16), f"seq {b}"
     assert np.array_equal(steps[0], steps[1])
+
+
+# the prompt's rows and their first RMSNorm at the widths where the kernel's register rows change (full and
+# partly filled), row counts that leave a workgroup partly filled
+@pytest.mark.parametrize("hidden,layers,n_vis,n_text,act", [(1024, 1, 3, 2, "bf16"), (1280, 1, 0, 1, "bf16"),
+                                                            (4096, 1, 6, 1, "bf16"), (512, 2, 2, 5, "bf16"),
+                                                            (1280, 1, 4, 3, "f32"), (768, 2, 5, 1, "f32")])
+def test_prefill_embedding(gpu_lib, hidden, layers, n_vis, n_text, act):
+    import torch
+    cfg = synth.LlmConfig(hidden=hidden, n_q=4, n_kv=2, head_dim=64, inter=256, vocab=16384, layers=layers, name="llm_embed")
+    wt = synth.llm_weights(cfg, seed=6)
+    f32 = act == "f32"
+    vis = synth.vision_embeds(n_vis, cfg.hidden) if n_vis else np.zeros((0, cfg.hidden), np.float32)
+    ids = synth.text_ids(n_text, cfg.vocab)
+    table, pool = synth.block_tables([n_vis + n_text], cfg.block, seed=5)
+    kref = vlm.PagedKV(cfg.layers, pool, cfg.n_kv, cfg.block, cfg.head_dim)
+    ref, _ = vlm.llm_prefill(vis, ids, wt, cfg, kv=kref, table=table[0])
+    llm = gpu_lib.Llm(cfg, wt, act=gpu_lib.ACT_F32 if f32 else gpu_lib.ACT_BF16)
+    kv = gpu_lib.KvPool(llm, pool)
+    logits = torch.empty(cfg.vocab, dtype=torch.float32, device="cuda")
+    llm.prefill(torch.from_numpy(vis).cuda().to(torch.float32 if f32 else torch.bfloat16) if n_vis else None,
+                torch.from_numpy(ids).cuda(), torch.from_numpy(table[0]).cuda(), kv, logits=logits)
+    torch.cuda.synchronize()
+    assert vlm.max_rel_err(logits.cpu().numpy(), ref) < (sc.TOL_F32 if f32 else sc.TOL_BF16)
