@@ -16,9 +16,9 @@
 //    global access covers whole cache lines.
 // Requirements (checked by the host): N % 128 == 0, K % 64 == 0, 16-byte aligned rows, ldo % 4 == 0.
 #include <algorithm>
-#include <cmath>
 
 #include "common.hpp"
+#include "gemm_plan.hpp"
 #include "kernels.hpp"
 
 namespace nova {
@@ -35,6 +35,7 @@ __device__ __forceinline__ int xcd_contiguous(int b, int n) {
 constexpr int BK = 64;
 constexpr int PAD = 8;             // bf16 elements of row padding in LDS
 constexpr int LDK = BK + PAD;      // LDS row pitch (elements)
+static_assert(BK == kGemmStepK, "the plan counts 64-wide K steps");
 
 // Four consecutive outputs: one 16-byte (fp32) or 8-byte (bf16) store.
 template <typename OT>
@@ -867,22 +868,6 @@ static hipError_t launch_ring(const GemmArgs& p, hipStream_t s, int kslices) {
   return hipGetLastError();
 }
 
-// The tiles a problem may run as, and the coefficients of a launch's estimated time in us, fitted to
-// 2900 timings (bf16 normal data, weights from HBM; M 16..5184 on the encoder's and decoder's nine
-// projection shapes, 1..12 K slices; 80% of the timings lie within 12% of the fit): with at most one
-// workgroup per CU, step1 per 64-wide K step + fixed1; with more, step2 per K step + round2 per round
-// of workgroup slots, + fixed2.
-struct Tile {
-  int bm, bn, per_cu;       // workgroups per CU
-  float step1, fixed1, step2, round2, fixed2;
-};
-static constexpr Tile kTiles[] = {
-    {32, 64, 2, 0.205f, 2.4f, 0.292f, 0.0f, 4.5f},    {64, 64, 2, 0.264f, 2.8f, 0.388f, 0.1f, 4.6f},
-    {64, 128, 1, 0.408f, 3.6f, 0.390f, 2.0f, 3.0f},   {128, 128, 1, 0.520f, 4.6f, 0.523f, 3.4f, 1.9f},
-    {256, 128, 1, 0.810f, 6.0f, 0.854f, 6.3f, -1.2f}, {128, 256, 1, 0.840f, 6.0f, 0.855f, 6.5f, -0.3f},
-    {128, 128, 2, 0.860f, 4.4f, 0.937f, 3.2f, 4.0f},  {256, 256, 1, 1.280f, 9.5f, 1.344f, 12.2f, -2.4f}};
-constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
-
 template <typename OT, int EPI>
 static hipError_t launch_plan_tile(const GemmArgs& p, int tile, hipStream_t s, int kslices) {
   switch (tile) {
@@ -897,132 +882,54 @@ static hipError_t launch_plan_tile(const GemmArgs& p, int tile, hipStream_t s, i
   }
 }
 
-struct Plan {
-  int tile = -1, slices = 1;
-  int n1 = 0;               // columns of whole rounds that run first (0: one launch), the rest planned anew
-  double us = 1e30;
-};
-
-// Estimated time of `wgs` workgroups of tile t with `steps` K steps each, over weights of `bytes` (read
-// from HBM at 5 TB/s; the two bounds add as squares, which the timings near both fit best).
-static double tile_us(const Tile& t, long wgs, int steps, double bytes) {
-  const long slots = 256L * t.per_cu;
-  // a last round that is partly empty costs a whole one after a single round, and only its share
-  // after eight, when the workgroups have drifted apart (the 8-image QKV's 9.5 rounds take 9.5)
-  const double part = (double)wgs / (double)slots, whole = std::ceil(part);
-  const double rounds = whole - (whole - part) * std::min(1.0, (whole - 1.0) / 8.0);
-  const double us = wgs <= 256 ? steps * t.step1 + t.fixed1 : rounds * (steps * t.step2 + t.round2) + t.fixed2;
-  const double hbm = bytes / 5.0e6 + 2.0;
-  return std::sqrt(us * us + hbm * hbm);
-}
-
-// The plan of an M x N x K problem with the least estimated time: a tile, K slices (up to
-// max_slices, partials within ws_floats), and with `split_cols` the columns of whole rounds of one
-// tile first and the leftover columns, which would leave most of a last round idle, with another.
-static Plan plan_gemm(int M, int N, int K, int max_slices, size_t ws_floats, bool split_cols) {
-  Plan best;
-  for (int i = 0; i < kNumTiles; ++i) {
-    const Tile& t = kTiles[i];
-    if (N % t.bn) continue;
-    const int nm = (M + t.bm - 1) / t.bm;
-    const long tiles = (long)nm * (N / t.bn), slots = 256L * t.per_cu;
-    for (int sl = 1; sl <= max_slices; ++sl) {
-      const int steps = (K / BK + sl - 1) / sl;
-      if (sl > 1 && (K / BK - (sl - 1) * steps < 2 || (size_t)sl * M * N > ws_floats)) continue;
-      double us = tile_us(t, tiles * sl, steps, (double)N * K * 2);
-      if (sl > 1) {        // one more launch; the partials written and read, from the caches while they are few
-        const double bytes = (double)sl * M * N * 8;
-        us += 3.5 + bytes / (bytes < 64e6 ? 10.0e6 : 5.0e6);
-      }
-      if (us < best.us) best = {i, sl, 0, us};
-    }
-    if (split_cols && tiles > slots && tiles % slots) {
-      const int n1 = (int)(tiles / slots * slots / nm) * t.bn;
-      if (n1 <= 0 || n1 >= N) continue;
-      const double us = tile_us(t, (long)nm * (n1 / t.bn), K / BK, (double)n1 * K * 2) + 2.0 +
-                        plan_gemm(M, N - n1, K, max_slices, ws_floats, false).us;
-      if (us < best.us) best = {i, 1, n1, us};
-    }
-  }
-  return best;
-}
-
+// K in `slices` of one tile: unsliced with the epilogue in the kernel, else fp32 partials, then their sum.
 template <typename OT, int EPI>
-static hipError_t launch_plan(const GemmArgs& p, hipStream_t s, bool split_cols) {
-  const int max_slices = EPI != EPI_POS && p.split_ws != nullptr && p.vt == nullptr ? 16 : 1;
-  // the position epilogue writes fp32 and reads the table: over many rows 256-wide tiles pay (41,472
-  // patches: 110 us against 122 us with 128x128 tiles)
-  if (EPI == EPI_POS && p.M > 4096 && p.N % 256 == 0) return launch_plan_tile<OT, EPI>(p, kNumTiles - 1, s, 1);
-  // one launch over all columns where the epilogue addresses more than the output by column (V^T, the
-  // position table) or the caller folds the slices
-  split_cols = split_cols && EPI != EPI_POS && p.vt == nullptr && p.slices_out == nullptr;
-  const Plan r = plan_gemm(p.M, p.N, p.K, max_slices, p.split_ws_floats, split_cols);
-  if (r.tile < 0) return hipErrorInvalidValue;
-  if (r.n1 > 0) {
-    GemmArgs a = p;
-    a.N = r.n1;
-    const hipError_t e = launch_plan_tile<OT, EPI>(a, r.tile, s, 1);
-    if (e != hipSuccess) return e;
-    GemmArgs b = p;
-    b.N = p.N - r.n1;
-    b.W = p.W + (size_t)r.n1 * p.ldw;
-    if (p.bias) b.bias = p.bias + r.n1;
-    b.out = out_at<OT, EPI>(p, 0, EPI == EPI_SWIGLU ? r.n1 / 2 : r.n1);
-    return launch_plan<OT, EPI>(b, s, false);
-  }
-  if (r.slices == 1) return launch_plan_tile<OT, EPI>(p, r.tile, s, 1);
+static hipError_t launch_slices(const GemmArgs& p, int tile, int slices, hipStream_t s) {
+  if (slices == 1) return launch_plan_tile<OT, EPI>(p, tile, s, 1);
   if constexpr (EPI != EPI_POS) {
     GemmArgs q = p;
     q.out = p.split_ws;
     q.ldo = p.N;
-    q.kslice = (p.K / BK + r.slices - 1) / r.slices * BK;
+    q.kslice = (p.K / BK + slices - 1) / slices * BK;
     q.split_stride = (long)p.M * p.N;
-    const hipError_t e = launch_plan_tile<float, EPI_STORE>(q, r.tile, s, r.slices);
-    return e != hipSuccess ? e : finish_slices<OT, EPI>(p, s, r.slices);
+    const hipError_t e = launch_plan_tile<float, EPI_STORE>(q, tile, s, slices);
+    return e != hipSuccess ? e : finish_slices<OT, EPI>(p, s, slices);
   }
   return hipErrorInvalidValue;
-}
-
-// Rows to run as 256x256 tiles ahead of the rest (0: no split): with more than 16 row tiles and a
-// last round of 256x256 tiles (one workgroup per CU) that would leave part of the GPU idle, the rows
-// of whole rounds go first and the leftover rows are planned by themselves.  *us gets the estimated
-// time of both.  The results are bit-identical to one launch when the rest runs unsplit (the same K
-// order per output).  The screenshot encode (53 row tiles): QKV 4 -> 3.5 rounds, MLP up 5 -> 4.5,
-// O and down 2 -> 1.5; the 8-image MLP down (162 x 5): 4 -> 3.5.
-static int row_split_rows(const GemmArgs& p, double* us) {
-  const int nm = (p.M + 255) / 256, nn = p.N / 256;
-  if (p.N % 256 || nm <= 16 || p.pos != nullptr) return 0;
-  const long tiles = (long)nm * nn, full = tiles / 256;
-  if (full < 1) return 0;
-  const int m1 = (int)(full * 256 / nn);
-  if (m1 < 1 || m1 >= nm) return 0;
-  const int max_slices = p.split_ws != nullptr && p.vt == nullptr ? 16 : 1;
-  *us = tile_us(kTiles[kNumTiles - 1], (long)m1 * nn, p.K / BK, (double)p.N * p.K * 2) + 2.0 +
-        plan_gemm(p.M - m1 * 256, p.N, p.K, max_slices, p.split_ws_floats, false).us;
-  return m1 * 256;
 }
 
 template <typename TA, typename OT, int EPI>
 static hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
   if constexpr (sizeof(TA) == 2) {
     if (p.small_tiles) return launch_dma<OT, EPI, 128, 128, 64, 64>(p, s);
-    double us = 1e30;
-    if (const int m1 = row_split_rows(p, &us)) {
-      if (us < plan_gemm(p.M, p.N, p.K, 1, 0, false).us) {
-        GemmArgs a = p;
-        a.M = m1;
-        hipError_t e = launch_dma<OT, EPI, 256, 256, 64, 128>(a, s);
-        if (e != hipSuccess) return e;
-        GemmArgs b = p;
-        b.M = p.M - m1;
-        b.A = reinterpret_cast<const bf16_t*>(p.A) + (size_t)m1 * p.lda;
-        b.out = out_at<OT, EPI>(p, m1, 0);
-        b.vt_row0 = p.vt_row0 + m1;
-        b.slices_out = nullptr;
-        return launch_plan<OT, EPI>(b, s, false);
-      }
+    constexpr bool POS = EPI == EPI_POS;
+    GemmProblem q{p.M, p.N, p.K, POS};
+    q.max_slices = !POS && p.split_ws != nullptr && p.vt == nullptr ? 16 : 1;
+    q.ws_floats = p.split_ws_floats;
+    q.split_rows = !POS;
+    // one launch over all columns where the epilogue addresses more than the output by column (V^T, the
+    // position table) or the caller folds the slices
+    q.split_cols = !POS && p.vt == nullptr && p.slices_out == nullptr;
+    const GemmPlan r = plan_gemm(q);
+    if (r.tile < 0) return hipErrorInvalidValue;
+    if (r.rows == 0 && r.cols == 0) return launch_slices<OT, EPI>(p, r.tile, r.slices, s);
+    GemmArgs a = p, b = p;
+    if (r.rows > 0) {
+      a.M = r.rows;
+      b.M = p.M - r.rows;
+      b.A = reinterpret_cast<const bf16_t*>(p.A) + (size_t)r.rows * p.lda;
+      b.out = out_at<OT, EPI>(p, r.rows, 0);
+      b.vt_row0 = p.vt_row0 + r.rows;
+      b.slices_out = nullptr;
+    } else {
+      a.N = r.cols;
+      b.N = p.N - r.cols;
+      b.W = p.W + (size_t)r.cols * p.ldw;
+      if (p.bias) b.bias = p.bias + r.cols;
+      b.out = out_at<OT, EPI>(p, 0, EPI == EPI_SWIGLU ? r.cols / 2 : r.cols);
     }
-    return launch_plan<OT, EPI>(p, s, true);
+    const hipError_t e = launch_plan_tile<OT, EPI>(a, r.tile, s, 1);
+    return e != hipSuccess ? e : launch_slices<OT, EPI>(b, r.tile2, r.slices2, s);
   } else {
     // the line between the tiles: 1280-wide encoder layer, 2304 patches (at most 720 tiles of 128x128)
     // 822 us with 128x128 tiles and 631 with 32x64; 15,552 patches (4880) 4886 and 5187
