@@ -78,3 +78,12 @@ def test_plans_fit(planner, proj):
                 assert not r.rows and not r.cols
             if vt:
                 assert not r.cols
+
+
+@pytest.mark.parametrize("proj", [p for n, p in PROJECTIONS if p[0] != POS], ids=[n for n, p in PROJECTIONS if p[0] != POS])
+def test_plan_is_the_least_estimate(planner, proj):
+    """No choice that could run instead has a lower estimate than the plan."""
+    for m in [*range(64, 4100, 97), *range(4104, 41480, 56)]:
+        r = plan(planner, proj, m)
+        for kw in (dict(rows=0), dict(cols=0), dict(rows=0, cols=0), dict(slices=1), dict(slices=1, rows=0, cols=0)):
+            assert r.us <= plan(planner, proj, m, **kw).us * (1 + 1e-12), (m, kw)
