@@ -7,27 +7,39 @@
 
 namespace nova {
 
-// The tiles a problem may run as, and the coefficients of a launch's estimated time in us, fitted to
-// 2900 timings (bf16 normal data, weights from HBM; M 16..5184 on the encoder's and decoder's nine
-// projection shapes, 1..12 K slices; 80% of the timings lie within 12% of the fit): with at most one
-// workgroup per CU, step1 per 64-wide K step + fixed1; with more, step2 per K step + round2 per round
-// of workgroup slots, + fixed2.
+// The tiles a problem may run as, and the coefficients of a launch's estimated time in us: with at most one
+// workgroup per CU step1 per 64-wide K step + fixed1; with one round of two per CU step2 + fixed2; with more,
+// step per K step + round per round of workgroup slots, + fixed; and the epilogue's term per round.  Fitted to
+// 8355 timings (bf16 normal data, weights from HBM, M 1..41472 on the encoder's and decoder's ten projections
+// with their own epilogues, 1..16 K slices, 32..256 CUs): 88% of the timings lie within 10% of the fit, and the
+// tile and slices it picks take 0.5% longer than the fastest ones on average, at most 15%.
 struct GemmTile {
   int bm, bn, per_cu;       // workgroups per CU
-  float step1, fixed1, step2, round2, fixed2;
+  float step1, fixed1, step2, fixed2, step, round, fixed;
 };
 static constexpr GemmTile kGemmTiles[] = {
-    {32, 64, 2, 0.205f, 2.4f, 0.292f, 0.0f, 4.5f},    {64, 64, 2, 0.264f, 2.8f, 0.388f, 0.1f, 4.6f},
-    {64, 128, 1, 0.408f, 3.6f, 0.390f, 2.0f, 3.0f},   {128, 128, 1, 0.520f, 4.6f, 0.523f, 3.4f, 1.9f},
-    {256, 128, 1, 0.810f, 6.0f, 0.854f, 6.3f, -1.2f}, {128, 256, 1, 0.840f, 6.0f, 0.855f, 6.5f, -0.3f},
-    {128, 128, 2, 0.860f, 4.4f, 0.937f, 3.2f, 4.0f},  {256, 256, 1, 1.280f, 9.5f, 1.344f, 12.2f, -2.4f}};
+    {32, 64, 2, 0.185f, 3.2f, 0.361f, 3.7f, 0.288f, 1.2f, 3.0f},
+    {64, 64, 2, 0.250f, 3.6f, 0.444f, 4.1f, 0.372f, 1.3f, 3.3f},
+    {64, 128, 1, 0.382f, 4.7f, 0.f, 0.f, 0.381f, 2.3f, 2.6f},
+    {128, 128, 1, 0.495f, 5.0f, 0.f, 0.f, 0.508f, 2.7f, 2.5f},
+    {256, 128, 1, 0.795f, 6.2f, 0.f, 0.f, 0.827f, 4.1f, 1.4f},
+    {128, 256, 1, 0.813f, 6.4f, 0.f, 0.f, 0.838f, 3.7f, 3.1f},
+    {128, 128, 2, 0.891f, 5.2f, 0.908f, 6.9f, 0.895f, 1.5f, 7.5f},
+    {256, 256, 1, 1.260f, 10.2f, 0.f, 0.f, 1.268f, 7.1f, 3.8f}};
 constexpr int kGemmTileCount = (int)(sizeof(kGemmTiles) / sizeof(kGemmTiles[0]));
 constexpr int kGemmTile256 = kGemmTileCount - 1;
 constexpr int kGemmStepK = 64;
 
+// What an epilogue adds to a 256x256 tile over the bf16 store, in us (Epi order: store, GELU, residual, position,
+// SwiGLU), and the fp32 partial store of a K slice.
+static constexpr float kGemmEpiUs[] = {0.0f, 7.5f, 3.8f, 2.5f, 5.4f};
+constexpr float kGemmPartialUs = -1.0f;
+// Bytes per output that the sum of the K slices reads and writes besides the partials, by epilogue.
+static constexpr float kGemmSumBytes[] = {2.f, 2.f, 8.f, 4.f, 1.f};
+
 struct GemmProblem {
   int M, N, K;
-  bool pos;                 // the position epilogue
+  int epi;                  // Epi
   int max_slices;           // K slices the epilogue allows, their partials within ws_floats
   size_t ws_floats;
   bool split_rows, split_cols;   // whether the problem may run as two launches over its rows or columns
@@ -42,16 +54,19 @@ struct GemmPlan {
   double us = 1e30;         // estimated time
 };
 
-// Estimated time of `wgs` workgroups of tile t with `steps` K steps each, over weights of `bytes` (read
-// from HBM at 5 TB/s; the two bounds add as squares, which the timings near both fit best).
-static inline double gemm_tile_us(const GemmTile& t, long wgs, int steps, double bytes) {
+// Estimated time of `wgs` workgroups of tile t with `steps` K steps each, over weights
+// of `bytes` (read from HBM; the two bounds add as squares, which the timings near both fit best).
+static inline double gemm_tile_us(const GemmTile& t, float epi_us, long wgs, int steps, double bytes) {
   const long slots = 256L * t.per_cu;
   // a last round that is partly empty costs a whole one after a single round, and only its share
-  // after eight, when the workgroups have drifted apart (the 8-image QKV's 9.5 rounds take 9.5)
+  // after ten, when the workgroups have drifted apart (the 8-image QKV's 9.5 rounds take 9.5)
   const double part = (double)wgs / (double)slots, whole = std::ceil(part);
-  const double rounds = whole - (whole - part) * std::min(1.0, (whole - 1.0) / 8.0);
-  const double us = wgs <= 256 ? steps * t.step1 + t.fixed1 : rounds * (steps * t.step2 + t.round2) + t.fixed2;
-  const double hbm = bytes / 5.0e6 + 2.0;
+  const double rounds = whole - (whole - part) * std::min(1.0, (whole - 1.0) / 10.0);
+  const double epi = epi_us * t.bm * t.bn / 65536.0;
+  const double us = wgs <= 256    ? steps * t.step1 + t.fixed1 + epi
+                    : whole <= 1 ? steps * t.step2 + t.fixed2 + epi * t.per_cu
+                                 : rounds * (steps * t.step + t.round + epi * t.per_cu) + t.fixed;
+  const double hbm = bytes / 7.3e6;
   return std::sqrt(us * us + hbm * hbm);
 }
 
@@ -65,10 +80,10 @@ static inline GemmPlan plan_one_launch(const GemmProblem& p) {
     for (int sl = 1; sl <= p.max_slices; ++sl) {
       const int ksteps = p.K / kGemmStepK, steps = (ksteps + sl - 1) / sl;
       if (sl > 1 && (ksteps - (sl - 1) * steps < 2 || (size_t)sl * p.M * p.N > p.ws_floats)) continue;
-      double us = gemm_tile_us(t, tiles * sl, steps, (double)p.N * p.K * 2);
-      if (sl > 1) {        // one more launch; the partials written and read, from the caches while they are few
-        const double bytes = (double)sl * p.M * p.N * 8;
-        us += 3.5 + bytes / (bytes < 64e6 ? 10.0e6 : 5.0e6);
+      double us = gemm_tile_us(t, sl > 1 ? kGemmPartialUs : kGemmEpiUs[p.epi], tiles * sl, steps, (double)p.N * p.K * 2);
+      if (sl > 1) {        // one more launch; the partials written and read
+        const double bytes = (8.0 * sl + kGemmSumBytes[p.epi]) * p.M * p.N;
+        us += 3.1 + bytes / 8.6e6;
       }
       if (us < best.us) {
         best = GemmPlan();
@@ -103,7 +118,7 @@ static inline GemmPlan plan_columns(const GemmProblem& p) {
     GemmProblem q = p;
     q.N = p.N - n1;
     const GemmPlan r = gemm_two_launches(
-        i, 0, n1, gemm_tile_us(t, (long)nm * (n1 / t.bn), p.K / kGemmStepK, (double)n1 * p.K * 2), plan_one_launch(q));
+        i, 0, n1, gemm_tile_us(t, kGemmEpiUs[p.epi], (long)nm * (n1 / t.bn), p.K / kGemmStepK, (double)n1 * p.K * 2), plan_one_launch(q));
     if (r.us < best.us) best = r;
   }
   return best;
@@ -124,7 +139,7 @@ static inline GemmPlan plan_rows(const GemmProblem& p) {
   GemmProblem q = p;
   q.M = p.M - m1 * 256;
   return gemm_two_launches(kGemmTile256, m1 * 256, 0,
-                           gemm_tile_us(kGemmTiles[kGemmTile256], (long)m1 * nn, p.K / kGemmStepK, (double)p.N * p.K * 2),
+                           gemm_tile_us(kGemmTiles[kGemmTile256], kGemmEpiUs[p.epi], (long)m1 * nn, p.K / kGemmStepK, (double)p.N * p.K * 2),
                            plan_one_launch(q));
 }
 
@@ -132,13 +147,16 @@ static inline GemmPlan plan_rows(const GemmProblem& p) {
 static inline GemmPlan plan_gemm(const GemmProblem& p) {
   // the position epilogue writes fp32 and reads the table: over many rows 256-wide tiles pay (41,472
   // patches: 110 us against 122 us with 128x128 tiles)
-  if (p.pos && p.M > 4096 && p.N % 256 == 0) {
+  if (p.epi == 3 && p.M > 4096 && p.N % 256 == 0) {
     GemmPlan r;
     r.tile = kGemmTile256, r.us = 0;
     return r;
   }
-  // one comparison of everything that may run: a row split set against a plan that may use neither slices nor
-  // columns won at one size in six of the 1280-wide residual projections, up to 14% behind the plan it replaced
+  // One comparison of everything that may run (a row split set against a plan that may use neither slices nor
+  // columns won although the plan it replaced had the lower estimate: at 896 of 4673 row counts from 4104 to
+  // 41,480 of the encoder's O projection and 547 of MLP down, by up to 14%).  No margin: 711 two-launch plans
+  // took 1% less than estimated, with a spread of 4%, and asking a split to save 2 to 4% more made the chosen
+  // plans 0 to 0.09% slower on average over 256 CUs and 0.12 to 0.23% over partitions.
   GemmPlan best = plan_one_launch(p);
   const GemmPlan rows = plan_rows(p), cols = plan_columns(p);
   if (rows.us < best.us) best = rows;

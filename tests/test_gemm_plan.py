@@ -10,8 +10,8 @@ import pytest
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_21301_amd", "csrc")
 SHIM = """
 #include "gemm_plan.hpp"
-extern "C" void plan(int M, int N, int K, int pos, int max_slices, unsigned long ws, int rows, int cols, int* v, double* us) {
-  const nova::GemmPlan r = nova::plan_gemm(nova::GemmProblem{M, N, K, pos != 0, max_slices, ws, rows != 0, cols != 0});
+extern "C" void plan(int M, int N, int K, int epi, int max_slices, unsigned long ws, int rows, int cols, int* v, double* us) {
+  const nova::GemmPlan r = nova::plan_gemm(nova::GemmProblem{M, N, K, epi, max_slices, ws, rows != 0, cols != 0});
   const int o[6] = {r.tile, r.slices, r.rows, r.cols, r.tile2, r.slices2};
   for (int i = 0; i < 6; ++i) v[i] = o[i];
   *us = r.us;
@@ -48,9 +48,9 @@ def plan(lib, proj, m, ws=None, slices=None, rows=None, cols=None):
     """The plan of one projection over m rows as the stages ask for it, or with one of the choices taken away."""
     epi, vt, n, k = proj
     sliced = epi != POS and not vt
-    ws = max(SLICE_FLOATS, 4 * m * n // 2) if ws is None else ws
+    ws = max(SLICE_FLOATS, 4 * m * 4608 if proj in PREFILL.values() else 2 * m * n) if ws is None else ws
     v, us = (C.c_int * 6)(), C.c_double()
-    lib.plan(m, n, k, int(epi == POS), (16 if sliced else 1) if slices is None else slices, C.c_ulong(ws),
+    lib.plan(m, n, k, epi, (16 if sliced else 1) if slices is None else slices, C.c_ulong(ws),
              int(epi != POS) if rows is None else rows, int(sliced) if cols is None else cols, v, C.byref(us))
     return Plan(*v, us.value)
 
@@ -78,6 +78,29 @@ def test_plans_fit(planner, proj):
                 assert not r.rows and not r.cols
             if vt:
                 assert not r.cols
+
+
+# Single launches timed on an MI355X (us, by (tile, K slices), the fastest first), at sizes where a split into two
+# launches is slower or not possible.  One 1008x1008 image's MLP up projection takes 86 us as two launches.
+TIMED = [
+    (ENCODE["up"], 5184, {(7, 1): 81.8, (6, 1): 92.7, (5, 1): 95.8, (4, 1): 96.8}),
+    (ENCODE["up"], 2304, {(7, 1): 44.5, (6, 1): 45.9, (3, 1): 47.2, (5, 1): 49.3}),
+    (ENCODE["o"], 5184, {(4, 1): 26.8, (5, 1): 27.5, (6, 1): 28.0, (3, 1): 30.5}),
+    (ENCODE["down"], 5184, {(5, 1): 76.4, (4, 1): 76.5, (6, 1): 80.0, (7, 2): 82.7}),
+    (ENCODE["down"], 1600, {(4, 3): 37.0, (5, 3): 37.9, (2, 1): 38.3, (6, 3): 39.2}),
+    (ENCODE["merge"], 576, {(4, 3): 36.8, (5, 3): 37.0, (2, 1): 39.8, (6, 3): 39.8}),
+    (ENCODE["patch"], 1600, {(2, 1): 9.5, (1, 1): 9.8, (3, 1): 10.6, (0, 1): 12.5}),
+    (PREFILL["qkv"], 203, {(3, 3): 20.0, (4, 6): 21.6, (5, 6): 22.0, (4, 5): 22.3}),
+    (PREFILL["down"], 1500, {(7, 3): 179.7, (7, 6): 200.4, (4, 3): 209.2}),
+]
+
+
+@pytest.mark.parametrize("proj,m,us", TIMED)
+def test_plan_against_timings(planner, proj, m, us):
+    """The plan runs as one launch that takes at most 9% longer than the fastest timed one."""
+    r = plan(planner, proj, m)
+    assert not r.rows and not r.cols
+    assert us.get((r.tile, r.slices), 1e9) <= 1.09 * min(us.values()), r
 
 
 @pytest.mark.parametrize("proj", [p for n, p in PROJECTIONS if p[0] != POS], ids=[n for n, p in PROJECTIONS if p[0] != POS])
