@@ -145,9 +145,11 @@ static inline GemmPlan plan_rows(const GemmProblem& p) {
 
 // The plan of a problem (tile < 0: none fits, N is no multiple of 64).
 static inline GemmPlan plan_gemm(const GemmProblem& p) {
-  // the position epilogue writes fp32 and reads the table: over many rows 256-wide tiles pay (41,472
-  // patches: 110 us against 122 us with 128x128 tiles)
-  if (p.epi == 3 && p.M > 4096 && p.N % 256 == 0) {
+  // The position epilogue's traffic grows with narrower tiles, which the estimate does not count: from two rounds of
+  // 256x256 tiles on it takes them.  N = 1280, K = 640, 256x256 against the best other tile: 41,472 rows (3.2 rounds)
+  // 120 and 126 us, 10,680 on 64 CUs (3.3) 79 and 85, 13,416 on 128 CUs (2.1) 61 and 61; below, the estimate decides:
+  // 13,416 (1.04) 49 and 42, 5184 (0.41) 25 and 17.
+  if (p.epi == 3 && p.N % 256 == 0 && (long)((p.M + 255) / 256) * (p.N / 256) >= 2 * 256L) {
     GemmPlan r;
     r.tile = kGemmTile256, r.us = 0;
     return r;

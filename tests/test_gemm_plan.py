@@ -90,6 +90,10 @@ TIMED = [
     (ENCODE["down"], 1600, {(4, 3): 37.0, (5, 3): 37.9, (2, 1): 38.3, (6, 3): 39.2}),
     (ENCODE["merge"], 576, {(4, 3): 36.8, (5, 3): 37.0, (2, 1): 39.8, (6, 3): 39.8}),
     (ENCODE["patch"], 1600, {(2, 1): 9.5, (1, 1): 9.8, (3, 1): 10.6, (0, 1): 12.5}),
+    (ENCODE["patch"], 5184, {(4, 1): 17.1, (6, 1): 17.4, (5, 1): 17.4, (3, 1): 19.8, (7, 1): 24.8}),
+    (ENCODE["patch"], 13416, {(6, 1): 41.7, (5, 1): 44.2, (4, 1): 44.3, (3, 1): 45.8, (7, 1): 49.2}),
+    (ENCODE["patch"], 20736, {(7, 1): 51.6, (6, 1): 56.6, (5, 1): 59.0}),
+    (ENCODE["patch"], 41472, {(7, 1): 120.0, (5, 1): 126.2, (4, 1): 126.4, (6, 1): 126.7}),
     (PREFILL["qkv"], 203, {(3, 3): 20.0, (4, 6): 21.6, (5, 6): 22.0, (4, 5): 22.3}),
     (PREFILL["down"], 1500, {(7, 3): 179.7, (7, 6): 200.4, (4, 3): 209.2}),
 ]
