@@ -1,5 +1,5 @@
 // Which tiles an M x N x K bf16 problem of the encode and prefill GEMM (k_gemm.hip) runs as: host code only,
-// chosen per call from the sizes by estimated time.
+// chosen per call from the sizes and the stream's compute units by estimated time.
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -12,7 +12,8 @@ namespace nova {
 // step per K step + round per round of workgroup slots, + fixed; and the epilogue's term per round.  Fitted to
 // 8355 timings (bf16 normal data, weights from HBM, M 1..41472 on the encoder's and decoder's ten projections
 // with their own epilogues, 1..16 K slices, 32..256 CUs): 88% of the timings lie within 10% of the fit, and the
-// tile and slices it picks take 0.5% longer than the fastest ones on average, at most 15%.
+// tile and slices it picks take 0.5% longer than the fastest ones on average, at most 15%.  Planned for 256 CUs
+// on a partition they took 15% longer on average, up to twice as long.
 struct GemmTile {
   int bm, bn, per_cu;       // workgroups per CU
   float step1, fixed1, step2, fixed2, step, round, fixed;
@@ -40,6 +41,7 @@ static constexpr float kGemmSumBytes[] = {2.f, 2.f, 8.f, 4.f, 1.f};
 struct GemmProblem {
   int M, N, K;
   int epi;                  // Epi
+  int cus;                  // compute units of the stream: its partition's, or the whole GPU's
   int max_slices;           // K slices the epilogue allows, their partials within ws_floats
   size_t ws_floats;
   bool split_rows, split_cols;   // whether the problem may run as two launches over its rows or columns
@@ -54,19 +56,21 @@ struct GemmPlan {
   double us = 1e30;         // estimated time
 };
 
-// Estimated time of `wgs` workgroups of tile t with `steps` K steps each, over weights
-// of `bytes` (read from HBM; the two bounds add as squares, which the timings near both fit best).
-static inline double gemm_tile_us(const GemmTile& t, float epi_us, long wgs, int steps, double bytes) {
-  const long slots = 256L * t.per_cu;
+// Estimated time of `wgs` workgroups of tile t, `steps` K steps each, over p's first `cols` weight rows (read from
+// HBM; the two bounds add as squares, which the timings near both fit best).
+static inline double gemm_tile_us(const GemmProblem& p, const GemmTile& t, long wgs, int steps, bool partials,
+                                  int cols) {
+  const int cus = p.cus;
+  const long slots = (long)cus * t.per_cu;
   // a last round that is partly empty costs a whole one after a single round, and only its share
   // after ten, when the workgroups have drifted apart (the 8-image QKV's 9.5 rounds take 9.5)
   const double part = (double)wgs / (double)slots, whole = std::ceil(part);
   const double rounds = whole - (whole - part) * std::min(1.0, (whole - 1.0) / 10.0);
-  const double epi = epi_us * t.bm * t.bn / 65536.0;
-  const double us = wgs <= 256    ? steps * t.step1 + t.fixed1 + epi
+  const double epi = (partials ? kGemmPartialUs : kGemmEpiUs[p.epi]) * t.bm * t.bn / 65536.0;
+  const double us = wgs <= cus    ? steps * t.step1 + t.fixed1 + epi
                     : whole <= 1 ? steps * t.step2 + t.fixed2 + epi * t.per_cu
                                  : rounds * (steps * t.step + t.round + epi * t.per_cu) + t.fixed;
-  const double hbm = bytes / 7.3e6;
+  const double hbm = (double)cols * p.K * 2 / 7.3e6;
   return std::sqrt(us * us + hbm * hbm);
 }
 
@@ -80,7 +84,7 @@ static inline GemmPlan plan_one_launch(const GemmProblem& p) {
     for (int sl = 1; sl <= p.max_slices; ++sl) {
       const int ksteps = p.K / kGemmStepK, steps = (ksteps + sl - 1) / sl;
       if (sl > 1 && (ksteps - (sl - 1) * steps < 2 || (size_t)sl * p.M * p.N > p.ws_floats)) continue;
-      double us = gemm_tile_us(t, sl > 1 ? kGemmPartialUs : kGemmEpiUs[p.epi], tiles * sl, steps, (double)p.N * p.K * 2);
+      double us = gemm_tile_us(p, t, tiles * sl, steps, sl > 1, p.N);
       if (sl > 1) {        // one more launch; the partials written and read
         const double bytes = (8.0 * sl + kGemmSumBytes[p.epi]) * p.M * p.N;
         us += 3.1 + bytes / 8.6e6;
@@ -111,14 +115,14 @@ static inline GemmPlan plan_columns(const GemmProblem& p) {
     const GemmTile& t = kGemmTiles[i];
     if (p.N % t.bn) continue;
     const int nm = (p.M + t.bm - 1) / t.bm;
-    const long tiles = (long)nm * (p.N / t.bn), slots = 256L * t.per_cu;
+    const long tiles = (long)nm * (p.N / t.bn), slots = (long)p.cus * t.per_cu;
     if (tiles <= slots || tiles % slots == 0) continue;
     const int n1 = (int)(tiles / slots * slots / nm) * t.bn;
     if (n1 <= 0 || n1 >= p.N) continue;
     GemmProblem q = p;
     q.N = p.N - n1;
-    const GemmPlan r = gemm_two_launches(
-        i, 0, n1, gemm_tile_us(t, kGemmEpiUs[p.epi], (long)nm * (n1 / t.bn), p.K / kGemmStepK, (double)n1 * p.K * 2), plan_one_launch(q));
+    const double first = gemm_tile_us(p, t, (long)nm * (n1 / t.bn), p.K / kGemmStepK, false, n1);
+    const GemmPlan r = gemm_two_launches(i, 0, n1, first, plan_one_launch(q));
     if (r.us < best.us) best = r;
   }
   return best;
@@ -132,15 +136,14 @@ static inline GemmPlan plan_columns(const GemmProblem& p) {
 static inline GemmPlan plan_rows(const GemmProblem& p) {
   const int nm = (p.M + 255) / 256, nn = p.N / 256;
   if (!p.split_rows || p.N % 256 || nm <= 16) return GemmPlan();
-  const long full = (long)nm * nn / 256;
+  const long full = (long)nm * nn / p.cus;
   if (full < 1) return GemmPlan();
-  const int m1 = (int)(full * 256 / nn);
+  const int m1 = (int)(full * p.cus / nn);
   if (m1 < 1 || m1 >= nm) return GemmPlan();
   GemmProblem q = p;
   q.M = p.M - m1 * 256;
-  return gemm_two_launches(kGemmTile256, m1 * 256, 0,
-                           gemm_tile_us(kGemmTiles[kGemmTile256], kGemmEpiUs[p.epi], (long)m1 * nn, p.K / kGemmStepK, (double)p.N * p.K * 2),
-                           plan_one_launch(q));
+  const double first = gemm_tile_us(p, kGemmTiles[kGemmTile256], (long)m1 * nn, p.K / kGemmStepK, false, p.N);
+  return gemm_two_launches(kGemmTile256, m1 * 256, 0, first, plan_one_launch(q));
 }
 
 // The plan of a problem (tile < 0: none fits, N is no multiple of 64).
@@ -149,7 +152,7 @@ static inline GemmPlan plan_gemm(const GemmProblem& p) {
   // 256x256 tiles on it takes them.  N = 1280, K = 640, 256x256 against the best other tile: 41,472 rows (3.2 rounds)
   // 120 and 126 us, 10,680 on 64 CUs (3.3) 79 and 85, 13,416 on 128 CUs (2.1) 61 and 61; below, the estimate decides:
   // 13,416 (1.04) 49 and 42, 5184 (0.41) 25 and 17.
-  if (p.epi == 3 && p.N % 256 == 0 && (long)((p.M + 255) / 256) * (p.N / 256) >= 2 * 256L) {
+  if (p.epi == 3 && p.N % 256 == 0 && (long)((p.M + 255) / 256) * (p.N / 256) >= 2L * p.cus) {
     GemmPlan r;
     r.tile = kGemmTile256, r.us = 0;
     return r;

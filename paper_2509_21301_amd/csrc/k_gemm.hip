@@ -903,7 +903,7 @@ static hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
   if constexpr (sizeof(TA) == 2) {
     if (p.small_tiles) return launch_dma<OT, EPI, 128, 128, 64, 64>(p, s);
     constexpr bool POS = EPI == EPI_POS;
-    GemmProblem q{p.M, p.N, p.K, EPI};
+    GemmProblem q{p.M, p.N, p.K, EPI, p.cus > 0 ? p.cus : 256};
     q.max_slices = !POS && p.split_ws != nullptr && p.vt == nullptr ? 16 : 1;
     q.ws_floats = p.split_ws_floats;
     q.split_rows = !POS;

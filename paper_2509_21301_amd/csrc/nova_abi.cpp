@@ -461,10 +461,12 @@ int vit_encode_t(nova_vit* v, const void* pixels, int B, void* out, void* ws, hi
   const VitBufs<T> d = vit_bufs<T>(v, B, ws);
   T *patches = d.patches, *a = d.a, *qkv = d.qkv, *vt = d.vt, *att = d.att, *hmlp = d.hmlp;
   float* x = d.x;
+  const int cus = stream_cus(s);
   // K-slice partials of a projection in the free bytes from `from` up to `to`
-  auto with_slices = [](GemmArgs& p, void* from, void* to) {
+  auto with_slices = [cus](GemmArgs& p, void* from, void* to) {
     p.split_ws = (float*)from;
     p.split_ws_floats = ((char*)to - (char*)from) / sizeof(float);
+    p.cus = cus;
   };
 
   const char* emb = (const char*)v->d.embed;
@@ -472,6 +474,7 @@ int vit_encode_t(nova_vit* v, const void* pixels, int B, void* out, void* ws, hi
   CALL(NOVA_KIND_MISC, s, nova::patchify<T>((const bf16_t*)pixels, B, c.image_h, c.image_w, c.patch, v->kpad, patches, s));
   {
     GemmArgs p{patches, v->kpad, ew(0), v->kpad, M, H, v->kpad, ew(1), x, H, ew(2), N};
+    p.cus = cus;
     CALL(NOVA_KIND_GEMM, s, (nova::gemm<T, T>(p, nova::EPI_POS, s)));
   }
   const int L = c.layers, K = v->offload ? v->d.n_slots : 0;
@@ -501,6 +504,7 @@ int vit_encode_t(nova_vit* v, const void* pixels, int B, void* out, void* ws, hi
     CALL(NOVA_KIND_MISC, s, nova::norm_rows<T>(x, M, H, W(0), W(1), c.eps, 1, a, H, 1, 0, 0, s));
     {
       GemmArgs p{a, H, W(2), H, M, 3 * H, H, W(3), qkv, 3 * H, nullptr, 0};
+      p.cus = cus;
       if (vt_fused) {      // V straight to V^T from the projection's epilogue
         p.vt = vt, p.v_col0 = 2 * H, p.vt_hd = hd, p.vt_tokens = N, p.vt_pad = skp;
       }
@@ -512,7 +516,7 @@ int vit_encode_t(nova_vit* v, const void* pixels, int B, void* out, void* ws, hi
       nova::AttnArgs p{qkv, 3L * H, (long)N * 3 * H, qkv + H, 3L * H, (long)N * 3 * H, vt, skp, att, H, (long)N * H,
                        N, N, heads, heads, B, 0};
       p.part = hmlp, p.part_bytes = (size_t)M * v->ip * sizeof(T);      // the MLP hidden is free here
-      p.cus = stream_cus(s);
+      p.cus = cus;
       CALL(NOVA_KIND_ATTN, s, nova::attention<T>(p, hd, s));
     }
     {
@@ -714,6 +718,7 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
   auto with_split = [&](GemmArgs p) {
     p.split_ws = split_ws;
     p.split_ws_floats = split_floats;
+    p.cus = cus;
     return p;
   };
 
@@ -1020,6 +1025,7 @@ extern "C" int nova_linear(int variant, const void* x, int M, int K, const void*
     case NOVA_LINEAR_TILED_SMALL: {
       if (K % 64 || N % 128) return fail(NOVA_EUNSUPPORTED, "tiled linear needs K %% 64 == 0 and N %% 128 == 0");
       GemmArgs p{xb, K, wb, K, M, N, K, nullptr, out, N, nullptr, 0};
+      p.cus = stream_cus(s);
       p.small_tiles = variant == NOVA_LINEAR_TILED_SMALL;
       CALL(NOVA_KIND_GEMM, s, (nova::gemm<bf16_t, bf16_t>(p, nova::EPI_RESID, s)));
       return NOVA_OK;
