@@ -87,7 +87,7 @@ static inline GemmPlan plan_one_launch(const GemmProblem& p) {
       double us = gemm_tile_us(p, t, tiles * sl, steps, sl > 1, p.N);
       if (sl > 1) {        // one more launch; the partials written and read
         const double bytes = (8.0 * sl + kGemmSumBytes[p.epi]) * p.M * p.N;
-        us += 3.1 + bytes / 8.6e6;
+        us += 3.1 + 0.2 * sl + bytes / 8.6e6;
       }
       if (us < best.us) {
         best = GemmPlan();

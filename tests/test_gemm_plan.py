@@ -102,6 +102,8 @@ TIMED = [
     (256, ENCODE["patch"], 20736, {(7, 1): 51.6, (6, 1): 56.6, (5, 1): 59.0}),
     (256, ENCODE["patch"], 41472, {(7, 1): 120.0, (5, 1): 126.2, (4, 1): 126.4, (6, 1): 126.7}),
     (256, PREFILL["qkv"], 203, {(3, 3): 20.0, (4, 6): 21.6, (5, 6): 22.0, (4, 5): 22.3}),
+    (256, PREFILL["qkv"], 1, {(0, 3): 10.7, (0, 2): 11.0, (0, 7): 11.8}),
+    (256, PREFILL["qkv"], 6, {(0, 3): 11.0, (0, 7): 12.1}),
     (256, PREFILL["down"], 1500, {(7, 3): 179.7, (7, 6): 200.4, (4, 3): 209.2}),
     (224, PREFILL["gate_up"], 1500, {(7, 1): 345.7, (5, 1): 441.1, (4, 1): 442.2}),
     (224, PREFILL["down"], 1500, {(7, 5): 208.1, (7, 2): 215.5, (7, 8): 219.9}),
