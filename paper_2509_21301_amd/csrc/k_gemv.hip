@@ -24,15 +24,12 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "gemv_plan.hpp"
 #include "kernels.hpp"
 
 namespace nova {
 
-constexpr int GV_KC = 256;             // K chunk per pipeline step (32 pieces of 8)
-constexpr int GV_RW = 16;              // weight rows per wave
-constexpr int GV_ROWS = 4 * GV_RW;     // rows per workgroup (4 waves)
 constexpr int GV_MAX_SPLITS = 16;
-constexpr int GV_TAIL_MAX = 4;         // K slices of a tail tile at most
 
 // K splits: as many as keep the workgroups (64 rows each) within the stream's compute units, one
 // workgroup per CU.  Measured on the decode shapes at 64, 128 and 256 CUs, a CU streams one
@@ -58,26 +55,6 @@ size_t gemv_partial_floats(int B, int N, int K, bool f32x, int cus) {
 // Element (row, k) of a 256-wide tile with rows of 32 16-byte pieces: piece k/8 is stored at
 // slot (k/8) ^ (row % 16).
 __device__ __forceinline__ int swz(int row, int piece) { return row * GV_KC + 8 * (piece ^ (row & 15)); }
-
-// The K slices of the gate/up projection's last row tiles.  With one workgroup per 64 rows, N / 64 = 592
-// tiles on 256 CUs are 2.3 rounds: 80 CUs stream three tiles while the others stream two.  The 80 tiles past
-// the last whole round are cut into the number of K slices (at most 4, as many as the workspace and the
-// arrival counters hold) that gives the busiest CU the least to stream: 3 slices, a third of a tile each.
-// Decode steps with and without (and with gate/up on the ring below 17 rows): batch 1, 4 layers 636 -> 624 us,
-// batch 8, 8 layers 1148 -> 1120, batch 32 at context 3627 872 -> 857, batch 8 on 128 CUs 850 -> 845.
-// 1: no slices.
-static int gemv_tail(const GemvArgs& p) {
-  const int tiles = p.N / GV_ROWS, tail = tiles % p.cus, chunks = p.K / GV_KC;
-  if (tiles < p.cus || tail == 0 || p.counters == nullptr || tail > p.n_counters || p.partial == nullptr) return 1;
-  int best = 1;
-  auto share = [&](int s) { return (double)((tail * s + p.cus - 1) / p.cus) * ((chunks + s - 1) / s) / chunks; };
-  for (int s = 2; s <= GV_TAIL_MAX; ++s) {
-    if ((s - 1) * ((chunks + s - 1) / s) >= chunks) continue;           // an empty slice
-    if ((size_t)s * tail * GV_ROWS * p.B > p.partial_floats) break;
-    if (share(s) < share(best)) best = s;
-  }
-  return best;
-}
 
 // One K slice's fp32 products of a tail tile (scaled by the row's norm already: the scale is a factor of
 // every slice) written through to the device-coherent level; the tile's last slice to arrive sums them in
@@ -579,14 +556,14 @@ static hipError_t gemv_launch(const GemvArgs& p, hipStream_t s) {
   const int kc = (chunks + splits - 1) / splits * GV_KC;
   dim3 grid(p.N / GV_ROWS, splits);
   if constexpr (!F32X && EPI != EPI_RESID) {
-    // 128-row workgroups while they make at least two rounds of two per CU
-    if (splits == 1 && p.N % 128 == 0 && p.N / 128 >= 4 * p.cus) {
+    if (splits == 1 && gemv_wide(p.N, p.cus)) {
       hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, true, NSCALE, true, 128>), dim3(p.N / 128), dim3(512), 0, s, p, kc);
       return hipGetLastError();
     }
   }
   if constexpr (EPI == EPI_SWIGLU) {
-    const int slices = splits == 1 ? gemv_tail(p) : 1;
+    const bool sums = p.counters != nullptr && p.partial != nullptr;
+    const int slices = splits == 1 && sums ? gemv_tail(p.N, p.K, p.B, p.cus, p.n_counters, p.partial_floats) : 1;
     if (slices > 1) {
       const int tiles = p.N / GV_ROWS, tail = tiles % p.cus;
       hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, true, NSCALE, RING, GV_ROWS, true>), dim3(tiles + tail * (slices - 1)),
