@@ -10,9 +10,20 @@ constexpr int GV_RW = 16;              // weight rows per wave
 constexpr int GV_ROWS = 4 * GV_RW;     // rows per workgroup (4 waves)
 constexpr int GV_TAIL_MAX = 4;         // K slices of a tail tile at most
 
-// Whether a bf16 projection whose K is not split runs as 128-row workgroups of the ring, which halve the X traffic
-// per weight: while they make at least two rounds of two per CU.
-static inline bool gemv_wide(int N, int cus) { return N % 128 == 0 && N / 128 >= 4 * cus; }
+// A bf16 projection whose K is not split and whose 128-row workgroups make at least two rounds of two per CU: rows
+// per workgroup of the ring (0: fewer rounds).  128 rows halve the X traffic per weight, 64 share the stream more
+// evenly, so the batch decides (us; K = 3584):
+//  * LM head, 152,064 rows, 128 / 64 rows: on 224 CUs 184 / 179 at batch 1, 192 / 188 at 8, 194 / 193 at 12; on
+//    160 194 / 185 at 1, 205 / 201 at 6, 214 / 221 at 12; on 128 222 / 211 at 1, 231 / 226 at 4, 241 / 245 at 8; on 64
+//    365 / 357 at 1, 374 / 376 at 4, 389 / 401 at 8.  On the whole GPU 180 / 182 at 1, 188 / 190 at 8, 203 / 214 at 32.
+//  * gate/up, 37,888 rows (two rounds on 74 CUs or fewer), 128 rows / 64 with the tail slices below: on 64 CUs
+//    100 / 92 at batch 1, 106 / 102 at 8, 108 / 107 at 12, 111 / 113 at 16, 126 / 144 at 32; on 32 183 / 168 at 1,
+//    194 / 189 at 8, 199 / 199 at 12, 206 / 211 at 16, 238 / 274 at 32.
+static inline int gemv_ring_rows(int N, int B, int cus, bool head, bool gate_up) {
+  if (N % 128 || N / 128 < 4 * cus) return 0;
+  if (head) return cus < 256 && B <= (cus >= 160 ? 8 : 4) ? 64 : 128;
+  return gate_up && B <= 12 ? 64 : 128;
+}
 
 // The K slices of the gate/up projection's last row tiles.  With one workgroup per 64 rows, N / 64 = 592
 // tiles on 256 CUs are 2.3 rounds: 80 CUs stream three tiles while the others stream two.  The 80 tiles past

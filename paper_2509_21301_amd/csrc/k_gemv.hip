@@ -556,9 +556,16 @@ static hipError_t gemv_launch(const GemvArgs& p, hipStream_t s) {
   const int kc = (chunks + splits - 1) / splits * GV_KC;
   dim3 grid(p.N / GV_ROWS, splits);
   if constexpr (!F32X && EPI != EPI_RESID) {
-    if (splits == 1 && gemv_wide(p.N, p.cus)) {
+    const int rows = splits == 1 ? gemv_ring_rows(p.N, p.B, p.cus, EPI == EPI_ARGMAX, EPI == EPI_SWIGLU) : 0;
+    if (rows == 128) {
       hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, true, NSCALE, true, 128>), dim3(p.N / 128), dim3(512), 0, s, p, kc);
       return hipGetLastError();
+    }
+    if constexpr (EPI == EPI_ARGMAX) {
+      if (rows == 64) {
+        hipLaunchKernelGGL((gemv_kernel<TA, OT, NB, EPI, true, NSCALE, true, GV_ROWS>), grid, dim3(256), 0, s, p, kc);
+        return hipGetLastError();
+      }
     }
   }
   if constexpr (EPI == EPI_SWIGLU) {

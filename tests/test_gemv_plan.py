@@ -9,7 +9,9 @@ import pytest
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_21301_amd", "csrc")
 SHIM = """
 #include "gemv_plan.hpp"
-extern "C" int wide(int N, int cus) { return nova::gemv_wide(N, cus); }
+extern "C" int rows(int N, int B, int cus, int head, int gate_up) {
+  return nova::gemv_ring_rows(N, B, cus, head != 0, gate_up != 0);
+}
 extern "C" int tail(int N, int K, int B, int cus, int counters, unsigned long floats) {
   return nova::gemv_tail(N, K, B, cus, counters, floats);
 }
@@ -43,3 +45,24 @@ def test_tail_slices_fit(rules):
                     if s > 1:
                         assert tiles >= cus and 0 < tiles % cus <= counters and s * (tiles % cus) * 64 * 7 <= floats
                         assert (s - 1) * -(-chunks // s) < chunks
+
+
+# us of the LM head and the gate/up projection (K = 3584) as 128-row and as 64-row workgroups, the latter with the
+# tail slices where the rule takes them: (weight rows, batch, CUs, 128 rows, 64 rows)
+WIDE = [(HEAD, 1, 256, 180, 182), (HEAD, 8, 256, 188, 190), (HEAD, 32, 256, 203, 214), (HEAD, 1, 224, 184, 179),
+        (HEAD, 8, 224, 192, 188), (HEAD, 32, 224, 212, 219), (HEAD, 1, 192, 190, 181), (HEAD, 8, 192, 200, 195),
+        (HEAD, 4, 160, 200, 193), (HEAD, 16, 160, 221, 232), (HEAD, 1, 128, 222, 211), (HEAD, 4, 128, 231, 226),
+        (HEAD, 12, 128, 247, 258), (HEAD, 1, 64, 365, 357), (HEAD, 8, 64, 389, 401), (HEAD, 32, 32, 904, 1081),
+        (GATE_UP, 1, 64, 100, 92), (GATE_UP, 8, 64, 106, 102), (GATE_UP, 17, 64, 114, 124), (GATE_UP, 32, 64, 126, 144),
+        (GATE_UP, 1, 32, 183, 168), (GATE_UP, 8, 32, 194, 189), (GATE_UP, 16, 32, 206, 211)]
+
+
+@pytest.mark.parametrize("n,b,cus,wide,narrow", WIDE)
+def test_rows_per_workgroup_against_timings(rules, n, b, cus, wide, narrow):
+    rows = rules.rows(n, b, cus, n == HEAD, n == GATE_UP)
+    assert (wide if rows == 128 else narrow) <= 1.01 * min(wide, narrow)
+
+
+def test_ring_rows_need_two_rounds(rules):
+    assert rules.rows(GATE_UP, 1, 76, 0, 1) == 0 and rules.rows(GATE_UP, 32, 256, 0, 1) == 0
+    assert rules.rows(64 * 1021, 1, 64, 1, 0) == 0                  # no multiple of 128

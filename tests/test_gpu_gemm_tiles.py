@@ -123,8 +123,9 @@ def test_thin_linear_ring(gpu_lib, m, k, n):
 
 
 # a head of 132,096 rows: the LM head's 128-row workgroups, one and two column groups, partly filled
-@pytest.mark.parametrize("bsz", [1, 16, 17, 32])
-def test_decode_wide_head(gpu_lib, bsz):
+# and on partitions, where small batches run it as 64-row workgroups
+@pytest.mark.parametrize("bsz,cus", [(1, 0), (16, 0), (17, 0), (32, 0), (3, 128), (5, 128), (8, 192)])
+def test_decode_wide_head(gpu_lib, bsz, cus):
     import torch
     cfg = synth.LlmConfig(hidden=256, n_q=4, n_kv=2, head_dim=64, inter=688, vocab=132096, layers=1, name="llm_head")
     wt = synth.llm_weights(cfg, seed=2)
@@ -140,8 +141,10 @@ def test_decode_wide_head(gpu_lib, bsz):
     kv.v5.copy_(torch.from_numpy(np.swapaxes(kref.v, -1, -2).astype(np.float32)).to(torch.bfloat16))
     ids, pos = synth.text_ids(bsz, cfg.vocab, seed=12), np.array(ctx, np.int32)
     logits = torch.full((bsz, cfg.vocab), float("nan"), dtype=torch.float32, device="cuda")
-    nxt = llm.decode(torch.from_numpy(ids).cuda(), torch.from_numpy(pos).cuda(), torch.from_numpy(tables).cuda(), kv,
-                     max_ctx=max(ctx) + 1, logits=logits)
+    stream = gpu_lib.set_stage_partition(gpu_lib.STAGE_DECODE, gpu_lib.make_cu_mask(cus)) if cus else None
+    args = [torch.from_numpy(a).cuda() for a in (ids, pos, tables)]
+    torch.cuda.synchronize()
+    nxt = llm.decode(*args, kv, max_ctx=max(ctx) + 1, logits=logits, stream=stream)
     torch.cuda.synchronize()
     ref, _ = vlm.llm_decode_step(ids, pos, tables, kref, wt, cfg)
     got = logits.cpu().numpy()
@@ -152,10 +155,11 @@ def test_decode_wide_head(gpu_lib, bsz):
 
 # gate/up of 8 x units row tiles: 8 or 32 tiles past the GPU's 256 compute units (one and two column groups,
 # 4 chunks of K over 2..4 slices), 40 (more than the arrival counters hold: no slices), 200 on a partition of
-# 64 compute units, and 264 tiles in fp32; a second step on the same workspace finds its counters zero again
+# 64 compute units, 520 there (64-row workgroups with slices at batch 12, 128-row ones at 13), and 264 tiles in
+# fp32; a second step on the same workspace finds its counters zero again
 @pytest.mark.parametrize("bsz,units,cus,act", [(1, 33, 0, "bf16"), (8, 36, 0, "bf16"), (17, 36, 0, "bf16"),
                                                (32, 33, 0, "bf16"), (5, 37, 0, "bf16"), (3, 25, 64, "bf16"),
-                                               (16, 33, 0, "f32")])
+                                               (12, 65, 64, "bf16"), (13, 65, 64, "bf16"), (16, 33, 0, "f32")])
 def test_decode_gate_up_tail(gpu_lib, bsz, units, cus, act):
     import torch
     cfg = synth.LlmConfig(hidden=1024, n_q=16, n_kv=4, head_dim=64, inter=256 * units, vocab=4096, layers=2, name="llm_tail")
