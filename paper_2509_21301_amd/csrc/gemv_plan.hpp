@@ -31,6 +31,10 @@ static inline int gemv_ring_rows(int N, int B, int cus, bool head, bool gate_up)
 // arrival counters hold) that gives the busiest CU the least to stream: 3 slices, a third of a tile each.
 // Decode steps with and without (and with gate/up on the ring below 17 rows): batch 1, 4 layers 636 -> 624 us,
 // batch 8, 8 layers 1148 -> 1120, batch 32 at context 3627 872 -> 857, batch 8 on 128 CUs 850 -> 845.
+// The slices' partials grow with the batch, so the larger batches take slices only for a larger part of a tile (gate/up
+// on the ring without / with slices, us): a saving of 0.14 of a tile (160 CUs) 52.6 / 51.9 at batch 1, 57.2 / 56.6 at 8,
+// 58.7 / 59.0 at 12, 60.9 / 62.2 at 16, 70.6 / 75.6 at 32; of 0.29 (128 CUs) 58.6 / 55.8, 71.0 / 70.3 at 16, 75.2 / 75.7
+// at 17, 83.4 / 84.4 at 32; of 0.5 (32 CUs) 240 / 236 at 17, 278 / 274 at 32; of 0.64 (256 CUs) 59.6 / 55.1 at 32.
 // 1: no slices.
 static inline int gemv_tail(int N, int K, int B, int cus, int counters, size_t partial_floats) {
   const int tiles = N / GV_ROWS, tail = tiles % cus, chunks = K / GV_KC;
@@ -42,7 +46,8 @@ static inline int gemv_tail(int N, int K, int B, int cus, int counters, size_t p
     if ((size_t)s * tail * GV_ROWS * B > partial_floats) break;
     if (share(s) < share(best)) best = s;
   }
-  return best;
+  const double most = B <= 12 ? 1.0 : B <= 16 ? 0.75 : 0.5;             // of a tile, left to the busiest CU
+  return share(best) <= most ? best : 1;
 }
 
 }  // namespace nova

@@ -66,3 +66,14 @@ def test_rows_per_workgroup_against_timings(rules, n, b, cus, wide, narrow):
 def test_ring_rows_need_two_rounds(rules):
     assert rules.rows(GATE_UP, 1, 76, 0, 1) == 0 and rules.rows(GATE_UP, 32, 256, 0, 1) == 0
     assert rules.rows(64 * 1021, 1, 64, 1, 0) == 0                  # no multiple of 128
+
+
+# us of the gate/up projection as 64-row workgroups without and with tail slices: (batch, CUs, without, with)
+TAIL = [(1, 256, 52.1, 48.5), (32, 256, 59.6, 55.1), (1, 192, 56.1, 48.5), (32, 192, 71.0, 62.3), (1, 160, 52.6, 51.9),
+        (8, 160, 57.2, 56.6), (16, 160, 60.9, 62.2), (17, 160, 63.6, 66.1), (32, 160, 70.6, 75.6), (1, 128, 58.6, 55.8),
+        (16, 128, 71.0, 70.3), (32, 128, 83.4, 84.4), (32, 96, 109.8, 102.2), (17, 32, 240.0, 236.5)]
+
+
+@pytest.mark.parametrize("b,cus,without,sliced", TAIL)
+def test_tail_slices_against_timings(rules, b, cus, without, sliced):
+    assert (sliced if slices(rules, b, cus) > 1 else without) <= 1.01 * min(without, sliced)
