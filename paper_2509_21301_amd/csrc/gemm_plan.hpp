@@ -169,4 +169,18 @@ static inline GemmPlan plan_gemm(const GemmProblem& p) {
   return best;
 }
 
+// fp32 activations: whether the 32x64 tiles run (gemm_f32_small_kernel) rather than the 128x128 ones, which take a
+// whole round of one workgroup per CU however few tiles it holds.  32x64 / 128x128 tiles, us:
+//  * 256 CUs, N and K 1280..5120: 20 tiles of 128x128 12.1 / 37.2, 180 35.9 / 45.3, but 240 47.3 / 45.9 and 250
+//    (K = 5120) 179 / 160; 320 58.6 / 86.8, 720 125 / 134, but 750 136 / 129; 960 161 / 170, 1000 179 / 178; from there
+//    on 1220 245 / 215, 1280 217 / 221, 1640 324 / 305, 2430 471 / 417, 4880 931 / 870: 128x128 tiles where the last of
+//    their rounds is nearly full, and beyond 1000 tiles;
+//  * partitions: a first round nearly full 47.5 / 37.5 (60 tiles on 64 CUs), but later ones on 128 CUs 250 80.6 / 86.1
+//    and 287 / 313 (K = 5120), 750 225 / 250, on 64 CUs 320 181 / 209: 128x128 tiles for the first only.
+static inline bool gemm_f32_small(int M, int N, int cus) {
+  const long tiles = (long)((M + 127) / 128) * (N / 128), last = (tiles - 1) % cus + 1;
+  const bool full = 8 * last >= 7L * cus;
+  return tiles <= 1000 && !(full && (tiles <= cus || cus > 192));
+}
+
 }  // namespace nova

@@ -931,9 +931,7 @@ static hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
     const hipError_t e = launch_plan_tile<OT, EPI>(a, r.tile, s, 1);
     return e != hipSuccess ? e : launch_slices<OT, EPI>(b, r.tile2, r.slices2, s);
   } else {
-    // the line between the tiles: 1280-wide encoder layer, 2304 patches (at most 720 tiles of 128x128)
-    // 822 us with 128x128 tiles and 631 with 32x64; 15,552 patches (4880) 4886 and 5187
-    if ((long)((p.M + 127) / 128) * (p.N / 128) <= 1000) {
+    if (gemm_f32_small(p.M, p.N, p.cus > 0 ? p.cus : 256)) {
       const unsigned wgs = (unsigned)((p.M + 31) / 32 * (p.N / 64));
       hipLaunchKernelGGL((gemm_f32_small_kernel<EPI>), dim3(wgs), dim3(256), 0, s, p);
       return hipGetLastError();

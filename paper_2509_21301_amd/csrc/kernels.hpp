@@ -42,8 +42,8 @@ struct GemmArgs {
   // ([slices][M][N]) for the caller to fold into out (split_norm_rows), and *slices_out gets the
   // slice count; otherwise *slices_out = 0 and out is complete
   int* slices_out = nullptr;
-  // bf16: compute units the launch's stream may use (its CU partition; 0: all 256): tiles, K slices and the split
-  // into two launches are chosen to fill these
+  // compute units the launch's stream may use (its CU partition; 0: all 256): tiles, K slices and the split into
+  // two launches are chosen to fill these
   int cus = 0;
 };
 template <typename TA, typename OT>

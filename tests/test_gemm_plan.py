@@ -17,6 +17,7 @@ extern "C" void plan(int M, int N, int K, int epi, int cus, int max_slices, unsi
   for (int i = 0; i < 6; ++i) v[i] = o[i];
   *us = r.us;
 }
+extern "C" int f32_small(int M, int N, int cus) { return nova::gemm_f32_small(M, N, cus); }
 extern "C" int tiles(int* v) {
   for (int i = 0; i < nova::kGemmTileCount; ++i) {
     v[2 * i] = nova::kGemmTiles[i].bm;
@@ -132,3 +133,17 @@ def test_plan_is_the_least_estimate(planner, name):
         r = plan(planner, proj, m)
         for kw in (dict(rows=0), dict(cols=0), dict(rows=0, cols=0), dict(slices=1), dict(slices=1, rows=0, cols=0)):
             assert r.us <= plan(planner, proj, m, **kw).us * (1 + 1e-12), (m, kw)
+
+
+# fp32 activations, us: (CUs, rows, N, 32x64 tiles, 128x128 tiles)
+F32 = [(256, 256, 1280, 12.1, 37.2), (256, 2304, 1280, 35.9, 45.3), (256, 1024, 3840, 47.3, 45.9),
+       (256, 3200, 1280, 179.0, 159.5), (256, 1024, 5120, 59.3, 89.7), (256, 4096, 1280, 58.6, 86.8),
+       (256, 2304, 3840, 95.3, 126.0), (256, 2304, 5120, 124.9, 133.7), (256, 3200, 3840, 136.4, 128.6),
+       (256, 15552, 1280, 244.9, 214.6), (256, 10368, 5120, 627.6, 565.0), (128, 256, 3840, 27.8, 38.0),
+       (128, 4000, 512, 14.7, 11.8), (128, 3200, 1280, 80.6, 86.1), (128, 2304, 5120, 210.5, 261.1),
+       (64, 256, 3840, 47.5, 37.5), (64, 1024, 1280, 53.0, 81.0), (64, 4096, 1280, 180.8, 209.4)]
+
+
+@pytest.mark.parametrize("cus,m,n,small,large", F32)
+def test_f32_tiles_against_timings(planner, cus, m, n, small, large):
+    assert (small if planner.f32_small(m, n, cus) else large) <= 1.03 * min(small, large)
