@@ -195,15 +195,15 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, const f32x4 (&a
   }
 }
 
-template <typename TA, typename OT, int EPI, int BM, int BN, int WM, int WN>
-__global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_kernel(GemmArgs p) {
-  constexpr bool F32A = sizeof(TA) == 4;
+// fp32 activations (exact mode): the operands of the next K step go through registers, A split into bf16 hi + lo.
+template <int EPI, int BM, int BN, int WM, int WN>
+__global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_f32_kernel(GemmArgs p) {
   constexpr int TM = WM / 16, TN = WN / 16;
   constexpr int WAVES_N = BN / WN;
   constexpr int NT = (BM / WM) * (BN / WN) * 64;     // threads per workgroup
   extern __shared__ __align__(16) unsigned char smem[];
-  bf16_t* As = reinterpret_cast<bf16_t*>(smem);                 // [2][BM][LDK] (x2 for hi/lo)
-  constexpr int A_ELEMS = BM * LDK * (F32A ? 2 : 1);
+  bf16_t* As = reinterpret_cast<bf16_t*>(smem);                 // [2][2 (hi, lo)][BM][LDK]
+  constexpr int A_ELEMS = 2 * BM * LDK;
   bf16_t* Bs = As + 2 * A_ELEMS;                                 // [2][BN][LDK]
   constexpr int B_ELEMS = BN * LDK;
 
@@ -224,13 +224,13 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_kernel(GemmAr
   const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   // ---- global -> register staging
-  constexpr int A_CHUNK = F32A ? 4 : 8;                 // elements per 16-byte chunk
+  constexpr int A_CHUNK = 4;                            // elements per 16-byte chunk
   constexpr int A_CPR = BK / A_CHUNK;                   // chunks per row
   constexpr int A_ITERS = BM * A_CPR / NT;
   constexpr int B_ITERS = BN * (BK / 8) / NT;
   static_assert(A_ITERS * NT == BM * A_CPR && B_ITERS * NT == BN * (BK / 8), "tile/thread mismatch");
   u32x4 ra[A_ITERS], rb[B_ITERS];
-  const TA* Ag = reinterpret_cast<const TA*>(p.A);
+  const float* Ag = reinterpret_cast<const float*>(p.A);
 
   auto load_global = [&](int k0) {
 #pragma unroll
@@ -252,20 +252,16 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_kernel(GemmAr
 #pragma unroll
     for (int i = 0; i < A_ITERS; ++i) {
       int c = tid + i * NT, row = c / A_CPR, col = (c % A_CPR) * A_CHUNK;
-      if constexpr (F32A) {
-        float x[4] = {__uint_as_float(ra[i][0]), __uint_as_float(ra[i][1]), __uint_as_float(ra[i][2]),
-                      __uint_as_float(ra[i][3])};
-        bf16_t h[4];
-        float l[4];
+      float x[4] = {__uint_as_float(ra[i][0]), __uint_as_float(ra[i][1]), __uint_as_float(ra[i][2]),
+                    __uint_as_float(ra[i][3])};
+      bf16_t h[4];
+      float l[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { h[j] = f2bf(x[j]); l[j] = x[j] - bf2f(h[j]); }
-        uint2 hv = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-        uint2 lv = make_uint2(pack2(l[0], l[1]), pack2(l[2], l[3]));
-        *reinterpret_cast<uint2*>(a + row * LDK + col) = hv;
-        *reinterpret_cast<uint2*>(a + BM * LDK + row * LDK + col) = lv;
-      } else {
-        *reinterpret_cast<u32x4*>(a + row * LDK + col) = ra[i];
-      }
+      for (int j = 0; j < 4; ++j) { h[j] = f2bf(x[j]); l[j] = x[j] - bf2f(h[j]); }
+      uint2 hv = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+      uint2 lv = make_uint2(pack2(l[0], l[1]), pack2(l[2], l[3]));
+      *reinterpret_cast<uint2*>(a + row * LDK + col) = hv;
+      *reinterpret_cast<uint2*>(a + BM * LDK + row * LDK + col) = lv;
     }
 #pragma unroll
     for (int i = 0; i < B_ITERS; ++i) {
@@ -304,21 +300,19 @@ __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64) gemm_kernel(GemmAr
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = mfma16(fa[i], fb[j], acc[i][j]);
-      if constexpr (F32A) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-          fa[i] = *reinterpret_cast<const Frag8*>(a + BM * LDK + (wm * WM + i * 16 + fr) * LDK + kk + fk);
+      for (int i = 0; i < TM; ++i)
+        fa[i] = *reinterpret_cast<const Frag8*>(a + BM * LDK + (wm * WM + i * 16 + fr) * LDK + kk + fk);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = mfma16(fa[i], fb[j], acc[i][j]);
-      }
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma16(fa[i], fb[j], acc[i][j]);
     }
     if (kt + 1 < nk) store_lds(cur ^ 1);
     __syncthreads();
   }
 
-  gemm_epilogue<OT, EPI, WM, WN>(p, acc, reinterpret_cast<float*>(smem), wave, lane, m0 + wm * WM, n0 + wn * WN);
+  gemm_epilogue<float, EPI, WM, WN>(p, acc, reinterpret_cast<float*>(smem), wave, lane, m0 + wm * WM, n0 + wn * WN);
 }
 
 // fp32 activations, few output tiles (exact mode): 32x64 tiles of 4 waves, the operands of the next 4 K
@@ -789,13 +783,11 @@ __global__ void __launch_bounds__(256) split_reduce_kernel(GemmArgs p, const flo
   }
 }
 
-template <typename TA, typename OT, int EPI, int BM, int BN, int WM, int WN>
-static hipError_t launch_tile(const GemmArgs& p, hipStream_t s) {
-  constexpr bool F32A = sizeof(TA) == 4;
-  const size_t lds = (size_t)2 * (BM * LDK * (F32A ? 2 : 1) + BN * LDK) * sizeof(bf16_t);
-  static_assert((size_t)(BM / WM) * (BN / WN) * 16 * (WN + 4) * 4 <=
-                (size_t)2 * (BM * LDK + BN * LDK) * sizeof(bf16_t), "epilogue scratch exceeds the tile buffers");
-  auto kern = gemm_kernel<TA, OT, EPI, BM, BN, WM, WN>;
+template <int EPI, int BM, int BN, int WM, int WN>
+static hipError_t launch_f32(const GemmArgs& p, hipStream_t s) {
+  constexpr size_t lds = (size_t)2 * (2 * BM * LDK + BN * LDK) * sizeof(bf16_t);
+  static_assert((size_t)(BM / WM) * (BN / WN) * 16 * (WN + 4) * 4 <= lds, "epilogue scratch exceeds the tile buffers");
+  auto kern = gemm_f32_kernel<EPI, BM, BN, WM, WN>;
   static bool attr_set = false;   // benign race: idempotent attribute
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -848,7 +840,6 @@ static hipError_t finish_slices(const GemmArgs& p, hipStream_t s, int slices) {
                      (const float*)p.split_ws, slices);
   return hipGetLastError();
 }
-
 
 template <typename OT, int EPI, int BM, int BN, int WM, int WN, int NST>
 static hipError_t launch_ring(const GemmArgs& p, hipStream_t s, int kslices) {
@@ -936,8 +927,8 @@ static hipError_t launch_epi(const GemmArgs& p, hipStream_t s) {
       hipLaunchKernelGGL((gemm_f32_small_kernel<EPI>), dim3(wgs), dim3(256), 0, s, p);
       return hipGetLastError();
     }
+    return launch_f32<EPI, 128, 128, 64, 64>(p, s);
   }
-  return launch_tile<TA, OT, EPI, 128, 128, 64, 64>(p, s);
 }
 
 template <typename TA, typename OT>
