@@ -8,7 +8,10 @@ one by one (through the C ABI, bf16, tolerance 2e-2):
   3 ranges merged by a second pass) -- every merged token;
 * prefill: one 3584-wide GQA layer (28/4 heads of 128, SwiGLU 18944, vocab 152064) over
   1300 visual embeddings + 200 text tokens, and over a screenshot's 3354 + 225 -- last-row logits,
-  greedy id, sampled K/V;
+  greedy id, sampled K/V (the only layer is the last one, whose attention past the last block of 128
+  queries and whose O and MLP projections past the last row are not computed);
+* prefill: two such layers over the same prompts (vocab 16384) -- the second layer's K and V at rows of every
+  block of 128 queries, which depend on the first layer's attention, O and MLP projections over all rows;
 * decode: 4 and 20 sequences with ragged contexts of 1200..1500 tokens in a shuffled paged cache
   (random bf16 K/V shared with the oracle) -- logits of every sequence and the appended K/V; the
   small batch runs the step with its RMSNorms folded into the projections, the large one with
@@ -80,7 +83,7 @@ def llm1():
 
 
 # 1500 tokens (the benchmark's prompt) and 3579 (a 1092x2408 screenshot's 3354 visual tokens and 225
-# text tokens, the serving prompt), whose MLP down projection runs as one unsplit 256x256 launch
+# text tokens, the serving prompt)
 @pytest.mark.parametrize("nv,nt", [(synth.LLM_VISION_TOKENS, synth.LLM_TEXT_TOKENS), (3354, 225)])
 def test_prefill_layer_real_width(gpu_lib, llm1, nv, nt):
     import torch
@@ -110,6 +113,42 @@ def test_prefill_layer_real_width(gpu_lib, llm1, nv, nt):
         blk, slot = table[0][p // 16], p % 16
         assert vlm.max_rel_err(k5[0, blk, :, slot, :], k[p]) < sc.TOL_BF16
         assert vlm.max_rel_err(v5[0, blk, :, :, slot], v[p]) < sc.TOL_BF16
+
+
+# the first of two layers: every row of its attention (all query blocks, the heaviest ones in key ranges), O, gate/up
+# and down projections and the residual's K-slice fold reaches the second layer's K and V, also on a partition, whose
+# tiles and slices differ
+@pytest.mark.parametrize("nv,nt,cus", [(synth.LLM_VISION_TOKENS, synth.LLM_TEXT_TOKENS, None), (3354, 225, None),
+                                       (synth.LLM_VISION_TOKENS, synth.LLM_TEXT_TOKENS, 96)])
+def test_prefill_inner_layer_real_width(gpu_lib, nv, nt, cus):
+    import torch
+    nova = gpu_lib
+    cfg = dataclasses.replace(synth.LLM_28, layers=2, vocab=16384)
+    w = synth.llm_weights(cfg, seed=0)
+    vis = synth.vision_embeds(nv, cfg.hidden)
+    ids = synth.text_ids(nt, cfg.vocab)
+    s = nv + nt
+    table, pool = synth.block_tables([s], cfg.block, seed=5)
+    llm = nova.Llm(cfg, w)
+    kv = nova.KvPool(llm, pool)
+    stream = None if cus is None else nova.set_stage_partition(nova.STAGE_PREFILL, nova.make_cu_mask(cus, 0))
+    emb = torch.from_numpy(vis).cuda().to(torch.bfloat16)
+    args = (torch.from_numpy(ids).cuda(), torch.from_numpy(table[0]).cuda())
+    torch.cuda.synchronize()
+    llm.prefill(emb, *args, kv, stream=stream)
+    torch.cuda.synchronize()
+    x = np.concatenate([vis, w["embed"][ids]], 0)
+    rows = np.array(sorted({*range(0, s, 128), *range(127, s, 640), *range(77, s, 256), nv - 1, nv, s - 2, s - 1}))
+    hid, _, _ = vlm.llm_layer_rows(x, w, 0, cfg, rows)
+    _, k, v = vlm._qkv(vlm.rms_norm(hid, w["l1.rms1.g"], cfg.eps), w, 1, cfg, rows)
+    blk, slot = table[0][rows // cfg.block], rows % cfg.block
+    gk = kv.k5[1].float().cpu().numpy()[blk, :, slot]
+    gv = kv.v5[1].float().cpu().numpy()[blk, :, :, slot]
+    ek = [vlm.max_rel_err(a, b) for a, b in zip(gk, k)]
+    ev = [vlm.max_rel_err(a, b) for a, b in zip(gv, v)]
+    print(f"layer 1, {len(rows)} rows: K {max(ek):.2e}, V {max(ev):.2e}")
+    assert max(ek) < sc.TOL_BF16, f"row {rows[np.argmax(ek)]}"
+    assert max(ev) < sc.TOL_BF16, f"row {rows[np.argmax(ev)]}"
 
 
 # the thin GEMMs split K by the stream's CU count: on a 64-CU partition the O and down
