@@ -6,7 +6,9 @@ carries per-stage throughput (encode patches/s at batch 1/4/8, prefill tok/s of 
 prompt, decode tok/s at batch 1/8/32 on the 28-layer GQA decoder), each stage's throughput
 against its CU share (XCD-balanced masks of 32..256 CUs), decode co-running with encode and
 with prefill on complementary partitions, the roofline position of the dominant kernel family,
-and the oracle's CPU time on a bounded sample.
+and the oracle's CPU time on a bounded sample.  ``--detail FILE`` also writes what would make
+that line tens of kilobytes long: offload against resident, the Pareto front, every serving run
+and one run's partition timeline.
 
 All inputs are seeded synthetic data of the workload shapes; weights are random N(0, 0.02)
 bf16 generated on the device.  Usage: python bench.py [--steps K] [--warmup W] [--gpus 1]
@@ -90,9 +92,12 @@ def vit_flops(cfg, batch):
 
 
 def prefill_flops(cfg, s):
+    """What the next token and the cache need: of the last layer K and V of every row, but Q, the attention, O and
+    the MLP for the last row only."""
     H, d = cfg.hidden, cfg.head_dim
-    lin = 2 * s * H * ((cfg.n_q + 2 * cfg.n_kv) * d + cfg.n_q * d + 3 * cfg.inter) * cfg.layers
-    attn = 2 * s * s * cfg.n_q * d * cfg.layers          # causal: half of 4 S^2 n_q d
+    kv, rest = 2 * H * 2 * cfg.n_kv * d, 2 * H * (2 * cfg.n_q * d + 3 * cfg.inter)      # per row and layer
+    lin = s * (kv + rest) * (cfg.layers - 1) + s * kv + rest
+    attn = 2 * s * s * cfg.n_q * d * (cfg.layers - 1) + 4 * s * cfg.n_q * d             # causal: half of 4 S^2 n_q d
     head = 2 * H * cfg.vocab
     return lin + head, attn
 
@@ -126,6 +131,20 @@ def gemm_traffic():
     if vals.get("kernel_source_sha256") != want or "traffic_bytes_per_launch" not in vals:
         return None
     return int(float(vals["traffic_bytes_per_launch"]))
+
+
+# ----------------------------------------------------------------------------- result line
+# per-run and per-split measurements, written to --detail; the result line would run to 47 KB with them
+DETAIL = ("offload", "pareto_front", "serving_runs", "partition_timeline", "adaptive_params")
+SERVING = ("mode", "rate_req_s", "max_e2e_s", "avg_e2e_s", "avg_tbt_ms", "chosen")
+
+
+def result_line(result):
+    """The one line of results: every measured value, of the serving summary its main columns."""
+    short = {k: v for k, v in result.items() if k not in DETAIL}
+    if "serving" in short:
+        short["serving"] = [{k: r[k] for k in SERVING if k in r} for r in short["serving"]]
+    return json.dumps(short)
 
 
 # ----------------------------------------------------------------------------- timing helpers
@@ -655,6 +674,8 @@ def main():
     ap.add_argument("--hbm-budget", action="store_true",
                     help="only the serving runs under an HBM budget: encoder layers offloaded (K = 2 slots), "
                          "KV pool capped at 40 GB, batch-32 decode (prints their JSON)")
+    ap.add_argument("--detail", default=None, help="also write the whole result, with the offload "
+                    "measurements, every serving run and the partition timeline, to this JSON file")
     ap.add_argument("--modes", nargs="+", default=None, help="restrict the serving modes")
     ap.add_argument("--linear-corun", action="store_true",
                     help="only the two-linear co-run study (inter-CU partitions vs intra-CU sharing; prints its JSON)")
@@ -833,7 +854,7 @@ def main():
                                   "hbm_gbs": round((wb + kvb) / (t / 1e3) / 1e9, 1),
                                   "hbm_frac": round((wb + kvb) / (t / 1e3) / 1e9 / HBM_PEAK_GBS, 3)}
     result["stages"] = stages
-    log(json.dumps(stages))
+    log(f"stages: {json.dumps(stages)}")
 
     # ---------------- CU-share curves and co-run (XCD-balanced partitions)
     if not args.no_sweep:
@@ -902,7 +923,10 @@ def main():
     if not args.no_cpu:
         log("timing the oracle on the host (bounded sample)")
         result["cpu_baseline"] = cpu_baseline(synth)
-    print(json.dumps(result), flush=True)
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(result, f)
+    print(result_line(result), flush=True)
 
 
 if __name__ == "__main__":
