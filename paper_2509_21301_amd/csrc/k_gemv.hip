@@ -1,15 +1,19 @@
 // Thin GEMM for the decode linears and the LM head: Y[B,N] = X[B,K] W[N,K]^T, B <= 32.
 //
 // Decode is bound by streaming the weights from HBM (the paper's Table 3 decode row and
-// Sec. 3.2.1).  Each wave owns 16 weight rows and walks K in 256-wide chunks.  A chunk is read
-// with eight 16-byte-per-lane loads, each covering two whole rows (2 x 512 contiguous bytes):
-// loads that touch only part of a cache line per row cost far more per byte on a CU, which shows
-// most when the stream runs on a fraction of the chip.  The chunk then passes through a
-// wave-private LDS tile into the MFMA 16x16x32 operand layout (row = lane % 16), with an XOR
-// swizzle that keeps both the writes and the reads free of bank conflicts.  The batch is the
-// other MFMA operand: X chunks stream through a two-slot LDS ring shared by the workgroup's four
-// waves, one barrier per chunk.  Weight and X loads run two chunks ahead in registers, issued in
-// the order they are consumed so that each wait covers only its own chunk.
+// Sec. 3.2.1).  Each wave owns 16 weight rows, the batch is the other MFMA 16x16x32 operand, and a
+// workgroup's waves share the batch rows through LDS.  Two ways to bring the operands in:
+//  * ring (bf16: gate/up, batches of more than 16 rows, large LM heads): X and W go global -> LDS by
+//    16-byte LDS-DMA loads in an XOR-swizzled layout, through a ring of stages of 64 along K, one
+//    barrier per stage; no staging registers, 64 or 128 weight rows per workgroup;
+//  * registers (the other projections of up to 16 rows, and fp32): K in 256-wide chunks, read with
+//    eight 16-byte-per-lane loads, each covering two whole rows (2 x 512 contiguous bytes): loads
+//    that touch only part of a cache line per row cost far more per byte on a CU, which shows most
+//    when the stream runs on a fraction of the chip.  The chunk passes through a wave-private LDS
+//    tile into the MFMA operand layout (row = lane % 16), with an XOR swizzle that keeps both the
+//    writes and the reads free of bank conflicts; X chunks stream through a two-slot LDS ring.
+//    Weight and X loads run two chunks ahead, issued in the order they are consumed so that each
+//    wait covers only its own chunk.
 // When N alone gives too few workgroups, K is split and a small second pass reduces the fp32
 // partials and applies the epilogue; otherwise the epilogue is applied directly.
 // RMSNorm folding (small decode batches): a residual producer (O, down projection) writes the
@@ -116,13 +120,11 @@ __device__ __forceinline__ void gemv_tail_finish(const GemvArgs& p, const f32x4 
 // rsqrt(mean x^2 + eps), from the producer's per-tile sums of squares.
 // RING (bf16): X and W come through a ring of LDS stages filled by LDS-DMA, 64 wide along K, instead of
 // through registers.  With more than 16 batch rows the register path moves 144 KB through LDS per 32 KB
-// of weights (write and read of W, write and four reads of X) and holds two chunks ahead in 160
-// registers; the ring moves 96 KB, needs no staging registers and keeps 32 KB of weights in flight per
-// workgroup.  ROWS: weight rows per workgroup.  128 rows halve the X traffic per weight; they pay where
-// they still make two rounds of workgroups (the LM head, one column group or two), and lose where they
-// do not (gate/up at batch 32: 60 us with 592 workgroups of 64 rows, 65 us with 296 of 128).
-// At batch 32: gate/up 61.9 -> 60.0 us, QKV 12.7 -> 11.6, LM head 231.9 -> 209 us; LM head at batch 8
-// 195 -> 190 us, at batch 1 182 -> 181 us.
+// of weights (write and read of W, write and four reads of X) and holds two chunks ahead in registers;
+// the ring moves 96 KB and keeps 32 KB of weights in flight per workgroup.  ROWS: weight rows per
+// workgroup (gemv_ring_rows holds the rule).  128 rows halve the X traffic per weight; they lose where
+// they do not make two rounds of workgroups (gate/up at batch 32: 60 us with 592 workgroups of 64 rows, 65
+// us with 296 of 128).  At batch 32: gate/up 61.9 -> 60.0 us, QKV 12.7 -> 11.6, LM head 231.9 -> 209 us.
 constexpr int GV_BK = 64;              // ring: K per stage
 
 // TAIL (SwiGLU): the row tiles past the last whole round of one workgroup per CU, p.N / 64 % cus of them,
@@ -133,7 +135,7 @@ __global__ void __launch_bounds__(ROWS * 4) gemv_kernel(GemvArgs p, int kc) {
   static_assert(ROWS == GV_ROWS || (RING && EPI != EPI_RESID), "wide workgroups: ring, no residual epilogue");
   static_assert(!TAIL || (EPI == EPI_SWIGLU && DIRECT && ROWS == GV_ROWS), "tail slices: SwiGLU in 64-row tiles");
   constexpr int NWV = ROWS / GV_RW;                       // waves
-  constexpr int GV_NST = ROWS == GV_ROWS ? 5 : 3;         // ring stages: 60 KB, two workgroups per CU
+  constexpr int GV_NST = ROWS == GV_ROWS ? 5 : 3;         // ring stages: 50-62 KB, two or three workgroups per CU
   using TX = TA;
   constexpr bool F32X = sizeof(TA) == 4;                  // X fp32, operands split into bf16 hi + lo
   constexpr int XROWS = 16 * NB;                          // batch rows held (B padded)
@@ -546,10 +548,11 @@ __global__ void gemv_reduce(GemvArgs p, int splits) {
 
 template <typename TA, typename OT, int NB, int EPI, bool NSCALE>
 static hipError_t gemv_launch(const GemvArgs& p, hipStream_t s) {
-  // gate/up takes the ring at every batch size: its 35 registers let three workgroups share a CU where the
-  // register path's 176 let two (4-layer decode steps, 8 sequences: 1118 against 1128 us for 8 layers, batch
-  // 1 623 against 625).  The split projections of up to 16 rows stay on the register path, which streams
-  // faster where a CU holds one workgroup (batch 8 on 128 CUs: 845 us against 888 with the ring).
+  // bf16 gate/up takes the ring at every batch size: up to 16 rows three workgroups share a CU (36 vector
+  // registers, 50 KB of LDS) where the register path's 172 registers let two (8-layer decode step at batch 8 1118
+  // us against 1128, 4-layer step at batch 1 623 against 625).  The split projections of up to 16 rows stay on
+  // the register path, which streams faster where a CU holds one workgroup (4-layer step at batch 8 on 128 CUs
+  // 845 us against 888 with the ring).
   constexpr bool F32X = sizeof(TA) == 4, RING = !F32X && (NB == 2 || EPI == EPI_SWIGLU);
   const int splits = gemv_splits(p.N, p.K, p.B, F32X, p.cus);
   const int chunks = p.K / GV_KC;

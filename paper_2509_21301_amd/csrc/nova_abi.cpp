@@ -381,12 +381,16 @@ extern "C" void nova_vit_destroy(nova_vit* v) {
 }
 
 namespace {
-// The encoder's buffers.  K-slice partials of a projection go to whatever is free around it: the MLP
-// down projection's to a..slices, the O projection's to slices and hmlp, the MLP up projection's to
-// qkv..slices, the merge's to att..hmlp (never over vt, whose key padding stays zero for the whole pass).
-// With few rows those are too small for the slices that fill the GPU (16 of M x H floats, at most 256
-// workgroups of 256x128 outputs), so `slices` adds what a..att, 2.5 M H floats in bf16, leaves missing;
-// it shrinks more slowly than those grow, so a larger batch's workspace always serves a smaller batch.
+// The encoder's buffers, in this order.  K-slice partials of a projection go to buffers that hold nothing
+// while it runs:
+//    O (reads att, adds into x)          slices, hmlp
+//    MLP up (reads a, writes hmlp)       qkv, att, slices
+//    MLP down (reads hmlp, adds into x)  a, qkv, att, slices
+//    merge (reads qkv, writes out)       att, slices, hmlp
+// and never to vt, whose key padding stays zero for the whole pass.  With few rows those are too small for the
+// slices that fill the GPU (16 of M x H floats, at most 256 workgroups of 256x128 outputs), so `slices` adds
+// what a..att, 2.5 M H floats in bf16, leaves missing; it shrinks more slowly than those grow, so a larger
+// batch's workspace always serves a smaller batch.
 template <typename T>
 struct VitBufs {
   T* patches;
@@ -608,11 +612,12 @@ extern "C" size_t nova_kv_bytes(const nova_llm* m, int num_blocks) {
 namespace {
 // K slices of a small problem's ring tiles: at most 256 workgroups of 256x128 outputs
 constexpr size_t kSliceFloats = (size_t)256 * 256 * 128;
-// Split-K partials of the prefill projections: up to 4 K slices of the widest split output.
-size_t prefill_split_floats(const nova_llm* m, int S) {
+// The prefill attention's key-range partials, in the buffer of the projections' K slices.
+size_t prefill_key_range_floats(const nova_llm* m, int S) {
   return (size_t)4 * S * std::max<size_t>(m->d.cfg.hidden, m->qkvw);
 }
-size_t prefill_split_floats_gemm(const nova_llm* m, int S) {
+// K slices of the prefill projections: 4 of the widest row (hidden or QKV), 16 while the rows are few.
+size_t prefill_slice_floats(const nova_llm* m, int S) {
   const size_t row = (size_t)S * std::max<size_t>(m->d.cfg.hidden, m->qkvw);
   return std::max<size_t>(4 * row, std::min<size_t>(16 * row, kSliceFloats));
 }
@@ -630,7 +635,7 @@ size_t prefill_ws(const nova_llm* m, int S, Carve* cv) {
   w.take<T>((size_t)S * c.n_q * c.head_dim);                     // attention out
   w.take<T>((size_t)S * m->ip);                                  // MLP hidden
   w.take<unsigned long long>(1);                                 // argmax key
-  w.take<float>(prefill_split_floats_gemm(m, S));                // split-K partials
+  w.take<float>(prefill_slice_floats(m, S));                     // K-slice partials
   w.take<unsigned>((size_t)c.n_q * ((S + 127) / 128));           // attention arrival counters
   return w.used;
 }
@@ -708,13 +713,13 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
   T* att = w.take<T>((size_t)S * qd);
   T* hm = w.take<T>((size_t)S * m->ip);
   unsigned long long* keys = w.take<unsigned long long>(1);
-  const size_t split_floats = prefill_split_floats_gemm(m, S);
+  const size_t split_floats = prefill_slice_floats(m, S);
   float* split_ws = w.take<float>(split_floats);
   const int n_cnt = c.n_q * ((S + 127) / 128);
   unsigned* att_cnt = w.take<unsigned>((size_t)n_cnt);
   const size_t kv_layer = (size_t)kv->num_blocks * c.n_kv * c.block * D;
   const int cus = stream_cus(s);
-  // the QKV, O and down projections may split K when their tiles cannot fill the GPU
+  // every projection may cut K into slices when its tiles cannot fill the stream's compute units
   auto with_split = [&](GemmArgs p) {
     p.split_ws = split_ws;
     p.split_ws_floats = split_floats;
@@ -759,9 +764,9 @@ int llm_prefill_t(const nova_llm* m, const T* vis, int n_vis, const int* ids, in
                                                   c.block, s, att_cnt, n_cnt));
     {
       nova::AttnArgs p{qkv, m->qkvw, 0, qkv + qd, m->qkvw, 0, vt, skp, att, qd, 0, S, S, c.n_q, c.n_kv, 1, 1};
-      // the split-K partials are free between the QKV and O projections: the attention's key
-      // ranges keep theirs there
-      p.part = split_ws, p.part_bytes = prefill_split_floats(m, S) * sizeof(float), p.counters = att_cnt, p.cus = cus;
+      // the K slices' buffer is free between the QKV and O projections: the attention's key ranges keep
+      // their partials there
+      p.part = split_ws, p.part_bytes = prefill_key_range_floats(m, S) * sizeof(float), p.counters = att_cnt, p.cus = cus;
       p.last_block = tail;
       CALL(NOVA_KIND_ATTN, s, nova::attention<T>(p, D, s));
     }
