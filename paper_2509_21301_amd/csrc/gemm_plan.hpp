@@ -9,7 +9,8 @@ namespace nova {
 
 // The tiles a problem may run as, and the coefficients of a launch's estimated time in us: with at most one
 // workgroup per CU step1 per 64-wide K step + fixed1; with one round of two per CU step2 + fixed2; with more,
-// step per K step + round per round of workgroup slots, + fixed; and the epilogue's term per round.  Fitted to
+// step per K step + round per round of workgroup slots, + fixed; and the epilogue's term per round.  (At K = 5120
+// the smaller tiles take 3 to 15% longer per step: 256 x 1280 x 5120 unsliced in 32x64 tiles 20.7 us.)  Fitted to
 // 8355 timings (bf16 normal data, weights from HBM, M 1..41472 on the encoder's and decoder's ten projections
 // with their own epilogues, 1..16 K slices, 32..256 CUs): 88% of the timings lie within 10% of the fit, and the
 // tile and slices it picks take 0.5% longer than the fastest ones on average, at most 15%.  Planned for 256 CUs
@@ -17,16 +18,17 @@ namespace nova {
 struct GemmTile {
   int bm, bn, per_cu;       // workgroups per CU
   float step1, fixed1, step2, fixed2, step, round, fixed;
+  float pitch;              // share that step1 and step2 grow by where rows of K lie a multiple of 2 KB apart
 };
 static constexpr GemmTile kGemmTiles[] = {
-    {32, 64, 2, 0.185f, 3.2f, 0.361f, 3.7f, 0.288f, 1.2f, 3.0f},
-    {64, 64, 2, 0.250f, 3.6f, 0.444f, 4.1f, 0.372f, 1.3f, 3.3f},
-    {64, 128, 1, 0.382f, 4.7f, 0.f, 0.f, 0.381f, 2.3f, 2.6f},
-    {128, 128, 1, 0.495f, 5.0f, 0.f, 0.f, 0.508f, 2.7f, 2.5f},
-    {256, 128, 1, 0.795f, 6.2f, 0.f, 0.f, 0.827f, 4.1f, 1.4f},
-    {128, 256, 1, 0.813f, 6.4f, 0.f, 0.f, 0.838f, 3.7f, 3.1f},
-    {128, 128, 2, 0.891f, 5.2f, 0.908f, 6.9f, 0.895f, 1.5f, 7.5f},
-    {256, 256, 1, 1.260f, 10.2f, 0.f, 0.f, 1.268f, 7.1f, 3.8f}};
+    {32, 64, 2, 0.185f, 3.2f, 0.361f, 3.7f, 0.288f, 1.2f, 3.0f, 0.15f},
+    {64, 64, 2, 0.250f, 3.6f, 0.444f, 4.1f, 0.372f, 1.3f, 3.3f, 0.10f},
+    {64, 128, 1, 0.382f, 4.7f, 0.f, 0.f, 0.381f, 2.3f, 2.6f, 0.08f},
+    {128, 128, 1, 0.495f, 5.0f, 0.f, 0.f, 0.508f, 2.7f, 2.5f, 0.03f},
+    {256, 128, 1, 0.795f, 6.2f, 0.f, 0.f, 0.827f, 4.1f, 1.4f, 0.f},
+    {128, 256, 1, 0.813f, 6.4f, 0.f, 0.f, 0.838f, 3.7f, 3.1f, 0.f},
+    {128, 128, 2, 0.891f, 5.2f, 0.908f, 6.9f, 0.895f, 1.5f, 7.5f, 0.f},
+    {256, 256, 1, 1.260f, 10.2f, 0.f, 0.f, 1.268f, 7.1f, 3.8f, 0.f}};
 constexpr int kGemmTileCount = (int)(sizeof(kGemmTiles) / sizeof(kGemmTiles[0]));
 constexpr int kGemmTile256 = kGemmTileCount - 1;
 constexpr int kGemmStepK = 64;
@@ -67,8 +69,9 @@ static inline double gemm_tile_us(const GemmProblem& p, const GemmTile& t, long 
   const double part = (double)wgs / (double)slots, whole = std::ceil(part);
   const double rounds = whole - (whole - part) * std::min(1.0, (whole - 1.0) / 10.0);
   const double epi = (partials ? kGemmPartialUs : kGemmEpiUs[p.epi]) * t.bm * t.bn / 65536.0;
-  const double us = wgs <= cus    ? steps * t.step1 + t.fixed1 + epi
-                    : whole <= 1 ? steps * t.step2 + t.fixed2 + epi * t.per_cu
+  const double first = steps * (p.K * 2 % 2048 ? 1.0 : 1.0 + t.pitch);
+  const double us = wgs <= cus    ? first * t.step1 + t.fixed1 + epi
+                    : whole <= 1 ? first * t.step2 + t.fixed2 + epi * t.per_cu
                                  : rounds * (steps * t.step + t.round + epi * t.per_cu) + t.fixed;
   const double hbm = (double)cols * p.K * 2 / 7.3e6;
   return std::sqrt(us * us + hbm * hbm);

@@ -96,6 +96,8 @@ TIMED = [
     (256, ENCODE["o"], 5184, {(4, 1): 26.8, (5, 1): 27.5, (6, 1): 28.0, (3, 1): 30.5}),
     (256, ENCODE["down"], 5184, {(5, 1): 76.4, (4, 1): 76.5, (6, 1): 80.0, (7, 2): 82.7}),
     (256, ENCODE["down"], 1600, {(4, 3): 37.0, (5, 3): 37.9, (2, 1): 38.3, (6, 3): 39.2}),
+    (256, ENCODE["down"], 312, {(2, 5): 17.0, (3, 8): 19.5}),
+    (256, ENCODE["down"], 360, {(3, 8): 18.0, (0, 1): 19.7}),
     (256, ENCODE["merge"], 576, {(4, 3): 36.8, (5, 3): 37.0, (2, 1): 39.8, (6, 3): 39.8}),
     (256, ENCODE["patch"], 1600, {(2, 1): 9.5, (1, 1): 9.8, (3, 1): 10.6, (0, 1): 12.5}),
     (256, ENCODE["patch"], 5184, {(4, 1): 17.1, (6, 1): 17.4, (5, 1): 17.4, (3, 1): 19.8, (7, 1): 24.8}),
