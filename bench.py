@@ -116,10 +116,10 @@ def gemm_traffic():
     """HBM bytes per GEMM call of the encode pass (one call of the GEMM routine, the unit timed
     below; the split problems launch two kernels per call), from the committed rocprofv3 PMC summary
     (FETCH_SIZE and WRITE_SIZE, each scaled by its reading for a plain 1 GiB copy); None when the
-    summary is missing or the GEMM source has changed since the counters were taken."""
+    summary is missing or the GEMM source or its tile plan has changed since the counters were taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "encode_gemm_hbm_traffic.md")
-    src = os.path.join(ROOT, "paper_2509_21301_amd", "csrc", "k_gemm.hip")
+    srcs = [os.path.join(ROOT, "paper_2509_21301_amd", "csrc", f) for f in ("k_gemm.hip", "gemm_plan.hpp")]
     if not os.path.exists(path):
         return None
     vals = {}
@@ -127,7 +127,7 @@ def gemm_traffic():
         if ":" in line and line.strip().startswith("- `"):
             k, v = line.strip()[3:].split("`", 1)
             vals[k] = v.strip(" :`")
-    want = hashlib.sha256(open(src, "rb").read()).hexdigest()
+    want = hashlib.sha256(b"".join(open(f, "rb").read() for f in srcs)).hexdigest()
     if vals.get("kernel_source_sha256") != want or "traffic_bytes_per_launch" not in vals:
         return None
     return int(float(vals["traffic_bytes_per_launch"]))
